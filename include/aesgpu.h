@@ -259,8 +259,8 @@ void aes_plan_destroy(aes_plan_t *plan);
 
 /* Kernel shapes of a context; read at every launch (tile_bytes when a plan is
  * created).  Defaults: tile 4096, CTR tiles 2 blocks per lane x 1024 threads,
- * CBC-decrypt tiles 2 blocks per lane x 1024 threads, chains four lanes each
- * (chain_quad = 1; chain_lanes = 64 when it is 0) x 256 threads, fused kernel
+ * CBC-decrypt tiles 2 blocks per lane x 1024 threads, chains several lanes
+ * each (chain_quad = 1; chain_lanes = 64 when it is 0) x 256 threads, fused kernel
  * 1 block per lane, fuse = 1, grid = 0 (one workgroup per compute unit),
  * ctr_variant = AES_CTR_TABLE. */
 typedef struct aes_launch_config {
@@ -270,7 +270,8 @@ typedef struct aes_launch_config {
     uint32_t dec_nb;      /* CBC-decrypt tile kernel: as ctr_nb */
     uint32_t dec_wg;      /* CBC-decrypt tile kernel: as ctr_wg */
     uint32_t chain_lanes; /* CBC-encrypt: chains (active lanes) per wave, 1..64 */
-    uint32_t chain_wg;    /* CBC-encrypt chain kernel: threads per workgroup */
+    uint32_t chain_wg;    /* CBC-encrypt chain kernel: threads per workgroup (not read for
+                             chains on sixteen lanes) */
     uint32_t mixed_nb;    /* fused mixed-batch kernel: blocks per lane (1, 2) */
     uint32_t fuse;        /* 1: a batch mixing CBC-encrypt chains with tiles runs as one launch
                              (batches without chains always run one launch per table set);
@@ -278,8 +279,9 @@ typedef struct aes_launch_config {
     uint32_t grid;        /* workgroups of tile and fused kernels; 0 = one per compute unit */
     uint32_t ctr_variant; /* CTR units of batches and plans: AES_CTR_TABLE or AES_CTR_BITSLICE */
     uint32_t chain_quad;  /* CBC-encrypt chains: 0 = chain_lanes chains per wave, one lane each;
-                             1 = 16 chains per wave, four lanes each (one state column per
-                             lane: a quarter of the lookups per lane per round) */
+                             1 = several lanes per chain: sixteen (one state byte per lane)
+                             while all chains then run at once, else four (one state
+                             column per lane) */
     uint32_t dec_variant; /* CBC- and ECB-decrypt units of batches and plans: AES_DEC_TABLE or
                              AES_DEC_BITSLICE (not tuned: aes_tune and its cache keep it) */
     uint32_t reserved[3];

@@ -320,7 +320,7 @@ struct aes_ctx {
     uint32_t tile_bytes = DEFAULT_TILE;
     TileLaunch tile_ctr;
     TileLaunch tile_dec;
-    ChainLaunch chain{256, 64, true, 0};  // four lanes per chain
+    ChainLaunch chain{256, 64, true, 0};  // several lanes per chain
     int mixed_nb = 1;        // fused kernel: 1 block per lane (its chain path takes the VGPRs)
     bool fuse = true;        // one launch for batches that mix ops
     int grid = 0;            // tile / fused kernel workgroups, 0 = one per compute unit
@@ -536,7 +536,10 @@ int launch_planned(aes_ctx *ctx, const PlanView &v, const aes_schedule_t *d_sche
                                    : v.ctr_bytes;
         a.n_dec_wg = dec_workgroups(fused, grid);
         a.chain_lanes = (uint32_t)ctx->chain.lanes;
-        a.chain_quad = ctx->chain.quad ? 1u : 0u;
+        // k_mixed gives chains half of the encryption waves when there are
+        // encryption tiles too, else all of them.
+        a.chain_width = (uint32_t)chain_lanes_for(
+            a.n_chain, ctx->chain.quad, (n_ctr_tab ? 8u : 16u) * ((uint32_t)grid - a.n_dec_wg));
         if ((e = launch_mixed(a, ctx->mixed_nb, grid, stream)))
             return hip_fail((hipError_t)e);
         return AES_OK;
@@ -1679,7 +1682,7 @@ int aes_tune(aes_ctx_t *ctx, const aes_req_t *reqs, uint64_t n_reqs, uint32_t n_
         c.chain_quad = 0;
         st = trial(c);
     }
-    if (!st && has_chains) {  // four lanes per chain
+    if (!st && has_chains) {  // several lanes per chain
         c = best;
         c.chain_quad = 1;
         st = trial(c);

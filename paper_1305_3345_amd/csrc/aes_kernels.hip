@@ -14,10 +14,12 @@ __device__ __forceinline__ uint32_t spread_wave(uint32_t wg, uint32_t n_wg) {
     return __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) * n_wg + wg);
 }
 
-// CBC-encrypt chains: cl chains per wave on one lane each, or (cl = 0) 16
-// chains per wave on four lanes each.
+// CBC-encrypt chains on W lanes each (W = 1: cl chains per wave).  The first
+// `waves` waves of a workgroup run chains; the others only help to fill the
+// tables.
+template <int W>
 __global__ __launch_bounds__(1024) void k_chains(const Unit *__restrict__ chains,
-                                                 uint32_t n_chain, uint32_t cl,
+                                                 uint32_t n_chain, uint32_t cl, uint32_t waves,
                                                  const aes_schedule_t *__restrict__ sched,
                                                  uint32_t n_sched,
                                                  const uint32_t *__restrict__ timg,
@@ -26,13 +28,12 @@ __global__ __launch_bounds__(1024) void k_chains(const Unit *__restrict__ chains
     fill_tables<false>(lds, timg);
     __syncthreads();
     const uint32_t lane = threadIdx.x & 63u;
+    if ((threadIdx.x >> 6) >= waves)
+        return;
     const uint32_t L0 = (lane & 31u) << 2;
-    const uint32_t n_waves = __builtin_amdgcn_readfirstlane(gridDim.x * (blockDim.x >> 6));
+    const uint32_t n_waves = __builtin_amdgcn_readfirstlane(gridDim.x * waves);
     const uint32_t e = spread_wave(blockIdx.x, gridDim.x);
-    if (cl)
-        chain_loop(lds, L0, lane, e, n_waves, cl, chains, n_chain, sched, n_sched, in, out);
-    else
-        chain_loop_quad(lds, L0, lane, e, n_waves, chains, n_chain, sched, n_sched, in, out);
+    chain_loop_any<W>(lds, L0, lane, e, n_waves, cl, chains, n_chain, sched, n_sched, in, out);
 }
 
 // ----------------------------------------------------- one fused launch
@@ -41,7 +42,7 @@ __global__ __launch_bounds__(1024) void k_chains(const Unit *__restrict__ chains
 // decryption tables and work the CBC-decrypt tiles; the others hold the
 // encryption tables, start the CBC-encrypt chains (the long serial work)
 // on their first waves, and every encryption wave then works CTR tiles.
-template <int NB, bool QUAD>
+template <int NB, int W>
 __global__ __launch_bounds__(1024) void k_mixed(MixedArgs a) {
     __shared__ uint32_t lds[LDS_DEC_WORDS];
     const uint32_t lane = threadIdx.x & 63u;
@@ -70,19 +71,15 @@ __global__ __launch_bounds__(1024) void k_mixed(MixedArgs a) {
     // share no registers.
     uint32_t cw = 0;
     if (a.n_chain) {
-        const uint32_t per_wave = QUAD ? 16u : a.chain_lanes;
+        const uint32_t per_wave = W == 1 ? a.chain_lanes : 64u / W;
         const uint32_t chain_waves = (uint32_t)(((uint64_t)a.n_chain + per_wave - 1) / per_wave);
         const uint32_t cap = a.n_ctr ? nw / 2u : nw;
         cw = chain_waves < cap ? chain_waves : cap;
         if (cw < 1u)
             cw = 1u;
         if (e < cw) {
-            if (QUAD)
-                chain_loop_quad(lds, L0, lane, e, cw, a.chains, a.n_chain, a.sched, a.n_sched,
-                                a.in, a.out);
-            else
-                chain_loop(lds, L0, lane, e, cw, a.chain_lanes, a.chains, a.n_chain, a.sched,
-                           a.n_sched, a.in, a.out);
+            chain_loop_any<W>(lds, L0, lane, e, cw, a.chain_lanes, a.chains, a.n_chain, a.sched,
+                              a.n_sched, a.in, a.out);
             return;
         }
     }
@@ -142,10 +139,11 @@ __global__ __launch_bounds__(1024) void k_request(aes_req_t r, uint32_t tile,
     const uint32_t L0 = (lane & 31u) << 2;
     const uint32_t L2 = L0 | SI_BASE;
     if (!DEC && r.op == AES_OP_CBC_ENC) {
-        // One serial chain, on four lanes of the first wave.
-        if (blockIdx.x == 0 && threadIdx.x < 64u) {
+        // One serial chain, on sixteen lanes of the first wave.
+        if (blockIdx.x == 0 && threadIdx.x < 64u && r.key_idx < n_sched) {
             const Unit un = request_unit(r, 0, (uint32_t)r.length);
-            run_chain_quad(lds, L0, lane, un, sched, n_sched, in, out);
+            const aes_schedule_t *ks = sched + r.key_idx;
+            run_chain_row(lds, L0, lane, un, ks->ek, ks->nr, in, out);
         }
         return;
     }
@@ -176,8 +174,10 @@ __global__ void k_snapshot_preds(const Unit *__restrict__ units, uint32_t n_unit
 
 // --------------------------------------------------------------- launchers
 
-static uint32_t chain_waves_needed(uint32_t n_chain, uint32_t cl) {
-    return (uint32_t)(((uint64_t)n_chain + cl - 1) / cl);
+int chain_lanes_for(uint32_t n_chain, bool grouped, uint32_t max_waves) {
+    if (!grouped)
+        return 1;
+    return n_chain <= 4ull * max_waves ? 16 : 4;
 }
 
 int launch_cbcenc_chains(const Unit *d_units, uint32_t n_units, const aes_schedule_t *d_sched,
@@ -186,21 +186,25 @@ int launch_cbcenc_chains(const Unit *d_units, uint32_t n_units, const aes_schedu
     if (!n_units)
         return hipSuccess;
     const uint32_t cl = cfg.lanes < 1 ? 64u : (cfg.lanes > 64 ? 64u : (uint32_t)cfg.lanes);
-    const int wpb = cfg.wg_threads / 64;
-    const uint32_t waves = chain_waves_needed(n_units, cfg.quad ? 16u : cl);
-    int grid = cfg.grid > 0 ? cfg.grid : (int)((waves + wpb - 1) / wpb);
-    if (grid > n_cu && cfg.grid <= 0)
-        grid = n_cu;
-    // Fewer waves than compute units: one wave per workgroup spreads them out.
-    int threads = cfg.wg_threads;
-    if (cfg.grid <= 0 && waves < (uint32_t)n_cu * wpb) {
-        const uint32_t per_cu = (waves + n_cu - 1) / n_cu;
-        threads = 64 * (int)(per_cu < 1 ? 1 : per_cu);
-        grid = (int)((waves + per_cu - 1) / per_cu);
+    const int w = chain_lanes_for(n_units, cfg.quad, 16u * (uint32_t)n_cu);
+    const uint32_t per_wave = w == 1 ? cl : 64u / (uint32_t)w;
+    const uint32_t need = (uint32_t)(((uint64_t)n_units + per_wave - 1) / per_wave);
+    // Waves of a workgroup (one per compute unit) that run chains: at most.
+    uint32_t waves = w == 16 ? 16u : (uint32_t)cfg.wg_threads / 64u;
+    uint32_t grid = cfg.grid > 0 ? (uint32_t)cfg.grid : (need + waves - 1) / waves;
+    if (cfg.grid <= 0 && grid > (uint32_t)n_cu)
+        grid = (uint32_t)n_cu;
+    // Fewer waves than compute units hold: spread over the compute units.
+    if (cfg.grid <= 0 && need < (uint32_t)n_cu * waves) {
+        waves = (need + n_cu - 1) / n_cu;
+        waves = waves < 1u ? 1u : waves;
+        grid = (need + waves - 1) / waves;
     }
-    hipLaunchKernelGGL(k_chains, dim3(grid < 1 ? 1 : grid), dim3(threads), 0,
-                       (hipStream_t)stream, d_units, n_units, cfg.quad ? 0u : cl, d_sched, n_sched,
-                       d_timg, d_in, d_out);
+    // At least four waves fill the tables.
+    const uint32_t threads = 64u * (waves < 4u ? 4u : waves);
+    const auto k = w == 16 ? &k_chains<16> : (w == 4 ? &k_chains<4> : &k_chains<1>);
+    hipLaunchKernelGGL(k, dim3(grid < 1 ? 1 : grid), dim3(threads), 0, (hipStream_t)stream,
+                       d_units, n_units, cl, waves, d_sched, n_sched, d_timg, d_in, d_out);
     return hipGetLastError();
 }
 
@@ -208,13 +212,14 @@ int launch_mixed(const MixedArgs &a, int nb, int grid, void *stream) {
     if (!a.n_dec && !a.n_ctr && !a.n_chain)
         return hipSuccess;
     void (*k)(MixedArgs) = nullptr;
+    const uint32_t w = a.chain_width;
     if (nb == 1)
-        k = a.chain_quad ? &k_mixed<1, true> : &k_mixed<1, false>;
+        k = w == 16 ? &k_mixed<1, 16> : w == 4 ? &k_mixed<1, 4> : w == 1 ? &k_mixed<1, 1> : nullptr;
     else if (nb == 2)
-        k = a.chain_quad ? &k_mixed<2, true> : &k_mixed<2, false>;
+        k = w == 16 ? &k_mixed<2, 16> : w == 4 ? &k_mixed<2, 4> : w == 1 ? &k_mixed<2, 1> : nullptr;
     if (!k || grid < 1 || (a.n_dec && a.n_dec_wg < 1) ||
         ((a.n_ctr || a.n_chain) && (uint32_t)grid <= a.n_dec_wg) || a.chain_lanes < 1 ||
-        a.chain_lanes > 64 || a.chain_quad > 1)
+        a.chain_lanes > 64)
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(k, dim3(grid), dim3(1024), 0, (hipStream_t)stream, a);
     return hipGetLastError();

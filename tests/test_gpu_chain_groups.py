@@ -122,3 +122,33 @@ def test_persistent_engine(ctx):
             assert done["status"] == 0, (off, int(done["status"]))
     torch.cuda.synchronize()
     check(d_out.cpu().numpy(), run_oracle(wl, inp), "persistent engine")
+
+
+@pytest.mark.parametrize("n,tiles,grid", [(3, 0, 0), (5, 2, 0), (16384, 0, 0), (16385, 0, 0),
+                                          (96, 3, 4), (97, 3, 4), (128, 0, 4), (131, 0, 4)])
+def test_chain_counts(fresh, n, tiles, grid):
+    """Chain counts around the changes of the chain kernels' form: waves that
+    are not full (four chains of sixteen lanes to a wave), and the last count
+    with sixteen lanes per chain and the first with four, alone (16,384 on 256
+    compute units) and in fused launches of four workgroups: one with the
+    decryption tables, three whose chain waves take 96 chains beside CTR
+    tiles; 128 and 131 chains as one launch of their own."""
+    print(f"[gpu] chain counts n={n} tiles={tiles} grid={grid}", flush=True)
+    fresh.set_config(chain_quad=1, fuse=1, grid=grid)
+    lengths = [16 * b for b in (BLOCKS[:12] * (n // 12 + 1))[:n]]
+    ops = [workloads.OP_CBC_ENC] * n
+    for i in range(tiles):
+        ops.append(workloads.OP_CBC_DEC if i == 0 else workloads.OP_CTR)
+        lengths.append(4096)
+    m = len(ops)
+    reqs = np.zeros(m, workloads.REQ_DTYPE)
+    reqs["length"] = np.asarray(lengths, np.uint64)
+    reqs["offset"][1:] = np.cumsum(reqs["length"] + 16)[:-1]
+    reqs["op"] = np.asarray(ops, np.uint32)
+    reqs["key_idx"] = np.arange(m) % 5 % 3
+    reqs["iv"] = gen.bytes_(n, gen.STREAM_IVS, 16 * m).reshape(m, 16)
+    keys, kb = workloads.make_keys(n, 3, [128, 192, 256])
+    wl = workloads.Workload("chain_counts", reqs, keys, kb,
+                            int(reqs["offset"][-1] + reqs["length"][-1] + 16), n)
+    inp = wl.data()
+    check(run_gpu(fresh, wl, inp, form="plan"), run_oracle(wl, inp), f"n={n} grid={grid}")
