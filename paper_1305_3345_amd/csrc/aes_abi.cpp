@@ -300,6 +300,7 @@ int plan_units(const aes_req_t *reqs, uint64_t n, uint32_t tile_bytes, bool grou
 
 struct Slot {
     void *h_stage = nullptr;  // pinned host staging for the unit table
+    void *d_stage = nullptr;  // the device's view of it
     size_t h_cap = 0;
     void *d_units = nullptr;  // device unit table + in-place predecessor snapshots
     size_t d_cap = 0;
@@ -370,7 +371,8 @@ size_t units_bytes(size_t n_dec, size_t n_ctr, size_t n_chain) {
 }
 
 struct PlanView {
-    void *d_units;
+    const void *d_units;  // unit table, in device memory or in pinned host memory
+    void *d_preds;        // in-place predecessor snapshots
     uint32_t *d_ctrs;  // 2 x TILE_CTRS zeroed counters of the tile launches
     size_t n_dec, n_ctr, n_chain;
     bool pred_in;
@@ -378,8 +380,11 @@ struct PlanView {
     size_t n_ecb;  // ECB-encrypt tiles: the last n_ecb of the n_ctr encryption tiles
 };
 
-PlanView view_of(const Planned &p, void *d_units, uint32_t *d_ctrs) {
-    return PlanView{d_units, d_ctrs, p.dec.size(), p.ctr.size(), p.chains.size(), p.dec_has_pred_in,
+// units: the table to launch from, d_units: the device allocation (its
+// snapshots follow the place of the table in it).
+PlanView view_of(const Planned &p, const void *units, void *d_units, uint32_t *d_ctrs) {
+    return PlanView{units, (Unit *)d_units + (p.dec.size() + p.ctr.size() + p.chains.size()),
+                    d_ctrs, p.dec.size(), p.ctr.size(), p.chains.size(), p.dec_has_pred_in,
                     p.dec_bytes, p.ctr_bytes, p.n_ecb};
 }
 
@@ -400,6 +405,15 @@ int alloc_tile_ctrs(uint32_t **out) {
     return AES_OK;
 }
 
+// Unit tables of up to this size are read by the kernels straight from the
+// pinned staging buffer, larger ones are uploaded.  An upload costs the host a
+// copy, an event and a wait (about 15 us a call, one 4 KiB request: 27.7 us a
+// call uploaded, 14.9 us read in place); reading in place costs the kernel the
+// link's latency and bandwidth (one unit 0.5 us, 1,024 units 1.4 us, 4,096
+// units 4 us, 8,000 to 32,768 units 5 to 7 us more than a table in device
+// memory).  At 8,192 units the two are even where the GPU is the limit.
+constexpr size_t DIRECT_UNITS_BYTES = 8192 * sizeof(Unit);
+
 // Takes the context's next staging slot for a call whose unit table has
 // ubytes bytes (need = device bytes with the in-place snapshots): waits for
 // the slot's last launch, then grows its pinned and device buffers if needed.
@@ -414,10 +428,15 @@ int take_slot(aes_ctx *ctx, size_t ubytes, size_t need, Slot **out) {
     if (s.h_cap < ubytes) {
         if (s.h_stage)
             (void)hipHostFree(s.h_stage);
-        s.h_stage = nullptr;
+        s.h_stage = s.d_stage = nullptr;
         s.h_cap = 0;
-        if (hipHostMalloc(&s.h_stage, ubytes, hipHostMallocDefault) != hipSuccess)
+        if (hipHostMalloc(&s.h_stage, ubytes, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
             return AES_ERR_NOMEM;
+        if (hipHostGetDevicePointer(&s.d_stage, s.h_stage, 0) != hipSuccess) {
+            (void)hipHostFree(s.h_stage);
+            s.h_stage = nullptr;
+            return AES_ERR_NOMEM;
+        }
         s.h_cap = ubytes;
     }
     if (s.d_cap < need) {
@@ -438,14 +457,21 @@ int take_slot(aes_ctx *ctx, size_t ubytes, size_t need, Slot **out) {
     return AES_OK;
 }
 
-// Uploads a slot's unit table for a launch on `stream`.  When the stream is
-// not being captured, the copy goes on the context's copy stream and the
-// launch waits for it by event, so the upload of one call overlaps the
-// kernels of the call before; under capture it stays on `stream`.  The slot
-// is free of earlier uploads and launches (its event was waited for).
-int upload_units(aes_ctx *ctx, Slot &s, size_t ubytes, void *stream) {
+// Makes a slot's unit table ready for a launch on `stream`; *units is where
+// the launch reads it.  A small table is read by the kernels from the pinned
+// staging buffer itself.  A larger one is uploaded: when the stream is not
+// being captured, the copy goes on the context's copy stream and the launch
+// waits for it by event, so the upload of one call overlaps the kernels of the
+// call before; under capture it stays on `stream`.  The slot is free of
+// earlier uploads and launches (its event was waited for).
+int upload_units(aes_ctx *ctx, Slot &s, size_t ubytes, void *stream, const void **units) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     HIP_TRY(hipStreamIsCapturing((hipStream_t)stream, &cap));
+    *units = s.d_units;
+    if (cap == hipStreamCaptureStatusNone && ubytes <= DIRECT_UNITS_BYTES) {
+        *units = s.d_stage;
+        return AES_OK;
+    }
     if (cap == hipStreamCaptureStatusNone && !ctx->copy &&
         hipStreamCreateWithFlags(&ctx->copy, hipStreamNonBlocking) != hipSuccess)
         ctx->copy = nullptr;
@@ -479,14 +505,13 @@ uint32_t dec_workgroups(const PlanView &v, int grid) {
 // Launches the kernels of one planned batch whose unit table is at v.d_units.
 int launch_planned(aes_ctx *ctx, const PlanView &v, const aes_schedule_t *d_scheds,
                    uint32_t n_scheds, const uint8_t *d_in, uint8_t *d_out, void *stream) {
-    Unit *u = (Unit *)v.d_units;
-    Unit *u_dec = u;
-    Unit *u_ctr = u + v.n_dec;
-    Unit *u_chain = u + v.n_dec + v.n_ctr;
+    const Unit *u_dec = (const Unit *)v.d_units;
+    const Unit *u_ctr = u_dec + v.n_dec;
+    const Unit *u_chain = u_ctr + v.n_ctr;
     void *d_preds = nullptr;
     int e;
     if (v.n_dec && v.pred_in && d_in == d_out) {
-        d_preds = (void *)(u + v.n_dec + v.n_ctr + v.n_chain);
+        d_preds = v.d_preds;
         if ((e = launch_snapshot_preds(u_dec, (uint32_t)v.n_dec, d_in, d_preds, stream)))
             return hip_fail((hipError_t)e);
     }
@@ -594,10 +619,11 @@ int run_batch(aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_scheds,
         return st;
     Slot &s = *sp;
     pack_units(p, s.h_stage);
-    if ((st = upload_units(ctx, s, ubytes, stream)))
+    const void *units = nullptr;
+    if ((st = upload_units(ctx, s, ubytes, stream, &units)))
         return st;
-    st = launch_planned(ctx, view_of(p, s.d_units, s.d_ctrs), d_scheds, n_scheds, d_in, d_out,
-                        stream);
+    st = launch_planned(ctx, view_of(p, units, s.d_units, s.d_ctrs), d_scheds, n_scheds, d_in,
+                        d_out, stream);
     if (st)
         return st;
     HIP_TRY(hipEventRecord(s.ev, (hipStream_t)stream));
@@ -781,7 +807,7 @@ int run_batch_noalloc(aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_s
     int e = launch_zero_words(d_ctrs, 2 * TILE_CTRS, stream);
     if (e)
         return hip_fail((hipError_t)e);
-    const PlanView v{d_scratch, d_ctrs, (size_t)n_dec, (size_t)(n_ctr + n_ecb), (size_t)n_chain,
+    const PlanView v{d_scratch, (Unit *)d_scratch + n_units, d_ctrs, (size_t)n_dec, (size_t)(n_ctr + n_ecb), (size_t)n_chain,
                      pred_in, dec_bytes, ctr_bytes, (size_t)n_ecb};
     return launch_planned(ctx, v, d_scheds, n_scheds, d_in, d_out, stream);
 }
@@ -947,10 +973,11 @@ int single_parallel(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds,
             }
         }
     });
-    if ((st = upload_units(ctx, s, ubytes, stream)))
+    const void *units = nullptr;
+    if ((st = upload_units(ctx, s, ubytes, stream, &units)))
         return st;
-    PlanView v{s.d_units, s.d_ctrs, n_dec, n_enc, 0, pred_in, dec ? payload : 0, dec ? 0 : payload,
-               op == AES_OP_ECB_ENC ? n_enc : 0};
+    PlanView v{units, (Unit *)s.d_units + n_tiles, s.d_ctrs, n_dec, n_enc, 0, pred_in,
+               dec ? payload : 0, dec ? 0 : payload, op == AES_OP_ECB_ENC ? n_enc : 0};
     st = launch_planned(ctx, v, d_scheds, n_scheds, d_in, d_out, stream);
     if (st)
         return st;
@@ -1238,7 +1265,7 @@ int aes_plan_launch(aes_plan_t *plan, const aes_schedule_t *d_scheds, const uint
     if (ctx->device == AES_DEVICE_NONE)
         return AES_ERR_DEVICE;
     HIP_TRY(hipSetDevice(ctx->device));
-    return launch_planned(ctx, view_of(plan->p, plan->d_units, plan->d_ctrs), d_scheds, plan->n_scheds, d_in,
+    return launch_planned(ctx, view_of(plan->p, plan->d_units, plan->d_units, plan->d_ctrs), d_scheds, plan->n_scheds, d_in,
                           d_out, stream);
 }
 
@@ -1447,7 +1474,7 @@ int aes_plan_graph(aes_plan_t *plan, const aes_schedule_t *d_scheds, const uint8
     if ((st = capture_stream(ctx)))
         return st;
     HIP_TRY(hipStreamBeginCapture(ctx->capture, hipStreamCaptureModeThreadLocal));
-    st = plan->p.payload ? launch_planned(ctx, view_of(plan->p, plan->d_units, plan->d_ctrs), d_scheds,
+    st = plan->p.payload ? launch_planned(ctx, view_of(plan->p, plan->d_units, plan->d_units, plan->d_ctrs), d_scheds,
                                           plan->n_scheds, d_in, d_out, ctx->capture)
                          : AES_OK;
     return finish_capture(ctx, st, 1, out);
@@ -1516,7 +1543,7 @@ int time_plan(aes_plan *plan, const aes_schedule_t *d_scheds, const uint8_t *d_i
     for (int i = 0; i <= iters && !st; i++) {
         hipError_t e = hipEventRecord(a, ctx->capture);
         if (e == hipSuccess) {
-            st = launch_planned(ctx, view_of(plan->p, plan->d_units, plan->d_ctrs), d_scheds, plan->n_scheds,
+            st = launch_planned(ctx, view_of(plan->p, plan->d_units, plan->d_units, plan->d_ctrs), d_scheds, plan->n_scheds,
                                 d_in, d_out, ctx->capture);
             if (!st)
                 e = hipEventRecord(b, ctx->capture);
