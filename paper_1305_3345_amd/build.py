@@ -19,10 +19,12 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 NO_PK_FP32 = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
-# Per-file instruction-scheduling strategy (LLVM AMDGPU), chosen by measuring
-# the tile kernels on 4 KiB pages: see each file's header.
-SCHED_FLAGS = {
+# Per-file code generation options (LLVM AMDGPU): the instruction-scheduling
+# strategy measured best for the tile kernels on 4 KiB pages, and kernel
+# arguments preloaded into scalar registers; see each file's header.
+FILE_FLAGS = {
     "aes_tiles_dec.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
+    "aes_tiles_short.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=16"],
 }
 
 
@@ -41,7 +43,7 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
     for src in sources():
         obj = os.path.join(objdir, os.path.basename(src) + ".o")
         objs.append(obj)
-        cmd = common + SCHED_FLAGS.get(os.path.basename(src), []) + ["-c", src, "-o", obj]
+        cmd = common + FILE_FLAGS.get(os.path.basename(src), []) + ["-c", src, "-o", obj]
         if src.endswith(".cpp"):
             cmd[cmd.index("-c"):cmd.index("-c")] = ["-x", "hip"]
         if verbose:

@@ -149,6 +149,7 @@ struct Planned {
     uint64_t payload = 0;
     uint64_t extent = 0;
     uint64_t dec_bytes = 0, ctr_bytes = 0, chain_bytes = 0;
+    uint32_t max_tile = 0;  // bytes of the largest tile
     bool dec_has_pred_in = false;
     size_t n_ecb = 0;  // ECB-encrypt tiles at the end of ctr
     std::vector<Unit> ecb;       // ECB-encrypt tiles while planning (appended to ctr)
@@ -162,6 +163,7 @@ struct Planned {
         ecb.clear();
         chains.clear();
         payload = extent = 0;
+        max_tile = 0;
         dec_bytes = ctr_bytes = chain_bytes = 0;
         dec_has_pred_in = false;
         n_ecb = 0;
@@ -243,6 +245,8 @@ int plan_units(const aes_req_t *reqs, uint64_t n, uint32_t tile_bytes, bool grou
                 continue;
             }
             const uint64_t ctr0 = be64(r.iv + 8);
+            p.max_tile = (uint32_t)std::max<uint64_t>(
+                p.max_tile, std::min<uint64_t>(tile_bytes, r.length));
             for (uint64_t pos = 0; pos < r.length; pos += tile_bytes) {
                 Unit u;
                 u.off = r.offset + pos;
@@ -377,6 +381,7 @@ struct PlanView {
     size_t n_dec, n_ctr, n_chain;
     bool pred_in;
     uint64_t dec_bytes, ctr_bytes;
+    uint32_t max_bytes;  // no tile is larger
     size_t n_ecb;  // ECB-encrypt tiles: the last n_ecb of the n_ctr encryption tiles
 };
 
@@ -385,7 +390,7 @@ struct PlanView {
 PlanView view_of(const Planned &p, const void *units, void *d_units, uint32_t *d_ctrs) {
     return PlanView{units, (Unit *)d_units + (p.dec.size() + p.ctr.size() + p.chains.size()),
                     d_ctrs, p.dec.size(), p.ctr.size(), p.chains.size(), p.dec_has_pred_in,
-                    p.dec_bytes, p.ctr_bytes, p.n_ecb};
+                    p.dec_bytes, p.ctr_bytes, p.max_tile, p.n_ecb};
 }
 
 // Zeroed tile-kernel counters for one plan or staging slot (the kernels
@@ -569,11 +574,11 @@ int launch_planned(aes_ctx *ctx, const PlanView &v, const aes_schedule_t *d_sche
             return hip_fail((hipError_t)e);
         return AES_OK;
     }
-    if ((e = launch_cbcdec_tiles(u_dec, (uint32_t)n_dec, d_scheds, n_scheds, ctx->d_timg,
+    if ((e = launch_cbcdec_tiles(u_dec, (uint32_t)n_dec, v.max_bytes, d_scheds, n_scheds, ctx->d_timg,
                                  d_preds, d_in, d_out, v.d_ctrs, ctx->tile_dec, ctx->n_cu,
                                  stream)))
         return hip_fail((hipError_t)e);
-    if ((e = launch_ctr_tiles(u_ctr, (uint32_t)n_ctr_tab, d_scheds, n_scheds, ctx->d_timg, d_in,
+    if ((e = launch_ctr_tiles(u_ctr, (uint32_t)n_ctr_tab, v.max_bytes, d_scheds, n_scheds, ctx->d_timg, d_in,
                               d_out, v.d_ctrs + TILE_CTRS, ctx->tile_ctr, ctx->n_cu, stream)))
         return hip_fail((hipError_t)e);
     if ((e = launch_cbcenc_chains(u_chain, (uint32_t)v.n_chain, d_scheds, n_scheds, ctx->d_timg,
@@ -688,7 +693,7 @@ int run_batch_noalloc(aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_s
     // 1. The per-request rules (as validate), order, and the unit counts.
     const uint32_t tile = ctx->tile_bytes;
     uint64_t n_dec = 0, n_ctr = 0, n_ecb = 0, n_chain = 0, n_live = 0, payload = 0;
-    uint64_t dec_bytes = 0, ctr_bytes = 0, last_off = 0;
+    uint64_t dec_bytes = 0, ctr_bytes = 0, last_off = 0, max_tile = 0;
     bool sorted = true, pred_in = false;
     for (uint64_t i = 0; i < n; i++) {
         const aes_req_t &r = reqs[i];
@@ -704,6 +709,8 @@ int run_batch_noalloc(aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_s
         n_live++;
         payload += r.length;
         const uint64_t t = (r.length + tile - 1) / tile;
+        if (r.op != AES_OP_CBC_ENC)
+            max_tile = std::max<uint64_t>(max_tile, std::min<uint64_t>(tile, r.length));
         if (r.op == AES_OP_CBC_ENC) {
             n_chain++;
         } else if (is_dec_tile_op(r.op)) {
@@ -808,7 +815,7 @@ int run_batch_noalloc(aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_s
     if (e)
         return hip_fail((hipError_t)e);
     const PlanView v{d_scratch, (Unit *)d_scratch + n_units, d_ctrs, (size_t)n_dec, (size_t)(n_ctr + n_ecb), (size_t)n_chain,
-                     pred_in, dec_bytes, ctr_bytes, (size_t)n_ecb};
+                     pred_in, dec_bytes, ctr_bytes, (uint32_t)max_tile, (size_t)n_ecb};
     return launch_planned(ctx, v, d_scheds, n_scheds, d_in, d_out, stream);
 }
 
@@ -825,7 +832,7 @@ struct ChunkScan {
     int err = AES_OK;
     bool ordered = true;  // nonzero requests in offset order and disjoint
     uint64_t first_off = UINT64_MAX, last_end = 0;
-    uint64_t tiles = 0, payload = 0, extent = 0;
+    uint64_t tiles = 0, payload = 0, extent = 0, longest = 0;
     bool pred_in = false;
 };
 
@@ -888,11 +895,12 @@ int single_parallel(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds,
             k.tiles += (len + tile - 1) / tile;
             k.payload += len;
             k.extent = std::max(k.extent, off + len);
+            k.longest = std::max(k.longest, len);
             k.pred_in |= dec && op == AES_OP_CBC_DEC && len > tile;
         }
     });
     // 2. The first error in request order, then disjointness.
-    uint64_t err_at = UINT64_MAX, payload = 0;
+    uint64_t err_at = UINT64_MAX, payload = 0, longest = 0;
     bool ordered = true, pred_in = false;
     uint64_t prev_end = 0;
     base[0] = 0;
@@ -906,6 +914,7 @@ int single_parallel(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds,
         if (sc[c].first_off != UINT64_MAX)
             prev_end = sc[c].last_end;
         payload += sc[c].payload;
+        longest = std::max(longest, sc[c].longest);
         pred_in |= sc[c].pred_in;
         base[c + 1] = base[c] + sc[c].tiles;
     }
@@ -977,7 +986,8 @@ int single_parallel(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds,
     if ((st = upload_units(ctx, s, ubytes, stream, &units)))
         return st;
     PlanView v{units, (Unit *)s.d_units + n_tiles, s.d_ctrs, n_dec, n_enc, 0, pred_in,
-               dec ? payload : 0, dec ? 0 : payload, op == AES_OP_ECB_ENC ? n_enc : 0};
+               dec ? payload : 0, dec ? 0 : payload,
+               (uint32_t)std::min<uint64_t>(tile, longest), op == AES_OP_ECB_ENC ? n_enc : 0};
     st = launch_planned(ctx, v, d_scheds, n_scheds, d_in, d_out, stream);
     if (st)
         return st;

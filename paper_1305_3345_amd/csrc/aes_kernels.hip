@@ -24,7 +24,7 @@ __global__ __launch_bounds__(1024) void k_chains(const Unit *__restrict__ chains
                                                  uint32_t n_sched,
                                                  const uint32_t *__restrict__ timg,
                                                  const uint8_t *in, uint8_t *out) {
-    __shared__ uint32_t lds[LDS_ENC_WORDS];
+    __shared__ __align__(16) uint32_t lds[LDS_ENC_WORDS];
     fill_tables<false>(lds, timg);
     __syncthreads();
     const uint32_t lane = threadIdx.x & 63u;
@@ -44,7 +44,7 @@ __global__ __launch_bounds__(1024) void k_chains(const Unit *__restrict__ chains
 // on their first waves, and every encryption wave then works CTR tiles.
 template <int NB, int W>
 __global__ __launch_bounds__(1024) void k_mixed(MixedArgs a) {
-    __shared__ uint32_t lds[LDS_DEC_WORDS];
+    __shared__ __align__(16) uint32_t lds[LDS_DEC_WORDS];
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t L0 = (lane & 31u) << 2;
     const uint32_t L2 = L0 | SI_BASE;
@@ -132,7 +132,7 @@ __global__ __launch_bounds__(1024) void k_request(aes_req_t r, uint32_t tile,
                                                  uint32_t n_sched,
                                                  const uint32_t *__restrict__ timg,
                                                  const uint8_t *in, uint8_t *out) {
-    __shared__ uint32_t lds[DEC ? LDS_DEC_WORDS : LDS_ENC_WORDS];
+    __shared__ __align__(16) uint32_t lds[DEC ? LDS_DEC_WORDS : LDS_ENC_WORDS];
     fill_tables<DEC>(lds, timg);
     __syncthreads();
     const uint32_t lane = threadIdx.x & 63u;
@@ -230,6 +230,9 @@ int launch_request(const aes_req_t &r, uint32_t tile, const aes_schedule_t *d_sc
                    uint8_t *d_out, int n_cu, void *stream) {
     if (!r.length)
         return hipSuccess;
+    int err;
+    if (launch_request_short(r, d_sched, n_sched, d_timg, d_in, d_out, n_cu, stream, &err))
+        return err;
     // A request's tiles spread over as many compute units as it has tiles
     // (one single-wave workgroup per tile for small requests); larger
     // requests get up to 16 waves per workgroup and up to two workgroups per

@@ -38,30 +38,73 @@ constexpr uint32_t SI_BASE = 0x20000u;     // byte address of Si4
 
 // ---------------------------------------------------------------- tables
 
-// Each thread loads table words from the 9 KiB image and writes the word's
-// 32 replicas itself, starting at replica (thread mod 32) so that the 32
-// threads of a half-wave hit 32 different banks on every store.
+// A thread writes the 32 replicas of a table word itself, 16 bytes at a time;
+// threads start at different 16-byte pieces of their 128-byte rows, and groups
+// of eight alternate between the two tables of a region (the two halves of its
+// 256-byte rows), so that consecutive threads hit different banks.  Four waves
+// fill the encryption tables in 2,450 clocks, sixteen in 2,050 (128 KiB at 128
+// bytes a clock is 1,024); one wave takes 7,300.
+
+// Word w (0..1023) of the four tables: its place in the image and in LDS (words).
+__device__ __forceinline__ void table_word(uint32_t w, uint32_t &src, uint32_t &dst) {
+    const uint32_t t = (w >> 9) * 2u + ((w >> 3) & 1u);
+    const uint32_t x = ((w & 511u) >> 4) * 8u + (w & 7u);
+    src = t * 256u + x;
+    dst = (t >> 1) * 16384u + x * 64u + (t & 1u) * 32u;
+}
+
+// Pieces first .. first + n - 1 (of eight, taken around) of the replicas of v.
+template <uint32_t N>
+__device__ __forceinline__ void write_replicas(uint32_t *lds, uint32_t dst, uint32_t first,
+                                               uint32_t v) {
+    const uint4 q = make_uint4(v, v, v, v);
+#pragma unroll
+    for (uint32_t j = 0; j < N; j++)
+        *reinterpret_cast<uint4 *>(lds + dst + ((j + first) & 7u) * 4u) = q;
+}
+
 template <bool DEC>
 __device__ __forceinline__ void fill_tables(uint32_t *lds, const uint32_t *__restrict__ timg) {
-    const uint32_t base = DEC ? 1024u : 0u;
-    const uint32_t nwords = DEC ? 1280u : 1024u;  // 4 tables (+ Si4)
-    const uint32_t rot = threadIdx.x & 31u;
+    constexpr uint32_t nwords = DEC ? 1280u : 1024u;  // 4 tables (+ Si4)
     for (uint32_t w = threadIdx.x; w < nwords; w += blockDim.x) {
-        uint32_t v, dst;
+        uint32_t src = 1024u + w, dst = 32768u + (w - 1024u) * 32u;
         if (w < 1024u) {
-            const uint32_t t = w >> 8, x = w & 255u;
-            v = timg[base + w];
-            dst = (t >> 1) * 16384u + x * 64u + (t & 1u) * 32u;
-        } else {
-            const uint32_t x = w - 1024u;
-            v = timg[2048u + x];
-            dst = 32768u + x * 32u;
+            table_word(w, src, dst);
+            src += DEC ? 1024u : 0u;
         }
-#pragma unroll
-        for (uint32_t j = 0; j < 32u; j++)
-            lds[dst + ((j + rot) & 31u)] = v;
+        write_replicas<8>(lds, dst, threadIdx.x, timg[src]);
     }
 }
+
+// The same for workgroups of BD (256, 512 or 1024) threads in two steps with
+// no branches, loads first: what is loaded between the two does not have to
+// arrive before the tables are written.
+template <bool DEC, uint32_t BD>
+struct TableFill {
+    static constexpr uint32_t N = 1024u / BD;
+    uint32_t v[N + 1];
+    __device__ __forceinline__ explicit TableFill(const uint32_t *__restrict__ timg) {
+#pragma unroll
+        for (uint32_t k = 0; k < N; k++) {
+            uint32_t src, dst;
+            table_word(threadIdx.x + k * BD, src, dst);
+            v[k] = timg[(DEC ? 1024u : 0u) + src];
+        }
+        if (DEC)
+            v[N] = timg[2048u + (threadIdx.x & 255u)];
+    }
+    __device__ __forceinline__ void store(uint32_t *lds) const {
+#pragma unroll
+        for (uint32_t k = 0; k < N; k++) {
+            uint32_t src, dst;
+            table_word(threadIdx.x + k * BD, src, dst);
+            write_replicas<8>(lds, dst, threadIdx.x, v[k]);
+        }
+        if (DEC)  // a word's replicas by the BD / 256 threads that loaded it
+            write_replicas<8 * 256 / BD>(lds, 32768u + (threadIdx.x & 255u) * 32u,
+                                         threadIdx.x + (threadIdx.x >> 8) * (8 * 256 / BD), v[N]);
+    }
+};
 
 // Three-input XOR in one VALU op (v_bitop3_b32, truth table 0x96 = a ^ b ^ c).
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {

@@ -454,7 +454,7 @@ __global__ void k_serve_reset(ServeQueue *q, uint32_t *closed) {
 // launch).  Every workgroup takes a whole compute unit's LDS, and the host
 // never launches more workgroups than the device holds at once.
 __global__ __launch_bounds__(512) void k_serve(ServeArgs a) {
-    __shared__ uint32_t lds[LDS_DEC_WORDS];
+    __shared__ __align__(16) uint32_t lds[LDS_DEC_WORDS];
     const bool dec = blockIdx.x >= gridDim.x - a.n_dec_wg;
     if (dec)
         fill_tables<true>(lds, a.timg);

@@ -1,0 +1,183 @@
+// aes_tiles_short.hip -- kernels and launchers over short_tiles.h: the units of
+// a small batch, or one request passed by value.  Built with kernel arguments
+// preloaded into scalar registers (a wave's first loads then have their
+// addresses at once).
+#include <hip/hip_runtime.h>
+#include <string.h>
+
+#include "internal.h"
+#include "short_tiles.h"
+
+namespace aesgpu {
+
+// A unit record on its way, the same in every lane (vector loads: scalar ones
+// would be waited for with the table lookups).
+struct RecordLoad {
+    uint4 a, b;
+    uint32_t u;
+    bool valid;
+    __device__ __forceinline__ Unit unit() const {
+        Unit un;
+        un.off = (uint64_t)__builtin_amdgcn_readfirstlane(a.y) << 32 |
+                 (uint32_t)__builtin_amdgcn_readfirstlane(a.x);
+        un.nbytes = __builtin_amdgcn_readfirstlane(a.z);
+        un.meta = __builtin_amdgcn_readfirstlane(a.w);
+        un.w[0] = __builtin_amdgcn_readfirstlane(b.x);
+        un.w[1] = __builtin_amdgcn_readfirstlane(b.y);
+        un.w[2] = __builtin_amdgcn_readfirstlane(b.z);
+        un.w[3] = __builtin_amdgcn_readfirstlane(b.w);
+        return un;
+    }
+};
+
+// 2^parts_log2 parts per unit; workgroup g takes the next `per` units, the first
+// `more` workgroups one more, so all parts of a unit are in one pass of one
+// workgroup.  (Quotient and remainder come from the host: a division here would
+// be a hundred instructions of cold code.)
+template <bool DEC, int NB, uint32_t BD>
+__global__ __launch_bounds__(BD) void k_tiles_short(
+    const Unit *__restrict__ units, uint32_t per, uint16_t more, uint16_t parts_log2,
+    const uint32_t *__restrict__ timg, const aes_schedule_t *__restrict__ sched, const uint8_t *in,
+    uint32_t n_sched, const uint4 *__restrict__ preds, uint8_t *out) {
+    __shared__ __align__(16) uint32_t lds[DEC ? LDS_DEC_WORDS : LDS_ENC_WORDS];
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t lo = blockIdx.x * per + (blockIdx.x < more ? blockIdx.x : more);
+    const uint32_t hi = lo + per + (blockIdx.x < more);
+    const uint32_t n_parts = (hi - lo) << parts_log2, last = hi - 1u;
+    const auto record = [&](uint32_t i) {
+        RecordLoad r;
+        r.u = lo + (i >> parts_log2);
+        r.valid = r.u < hi;
+        const uint4 *p = reinterpret_cast<const uint4 *>(units + (r.valid ? r.u : last));
+        // A per-lane address (of the same record) makes these vector loads.
+        uint32_t zero = 0;
+        asm("" : "+v"(zero));
+        r.a = p[zero];
+        r.b = p[1 + zero];
+        return r;
+    };
+    const auto load = [&](uint32_t i, const RecordLoad &r, Part<DEC, NB> &p) {
+        p.load(lane, r.unit(), r.valid, i & ((1u << parts_log2) - 1u),
+               preds ? preds + r.u : nullptr, sched, n_sched, in);
+    };
+    const TableFill<DEC, BD> fill(timg);
+    run_parts<DEC, NB, BD>(lds, fill, n_parts, in == out, record, load, in, out);
+}
+
+// One request as one unit; workgroup g takes the next `per` parts of it, the
+// first `more` workgroups one more.
+template <bool DEC, int NB, uint32_t BD>
+__global__ __launch_bounds__(BD) void k_request_short(
+    const uint32_t *__restrict__ timg, const aes_schedule_t *__restrict__ sched, const uint8_t *in,
+    uint64_t off, uint32_t nbytes, uint32_t meta, uint32_t per, uint32_t more, uint64_t w01,
+    uint64_t w23, uint32_t n_sched, uint8_t *out) {
+    __shared__ __align__(16) uint32_t lds[DEC ? LDS_DEC_WORDS : LDS_ENC_WORDS];
+    const TableFill<DEC, BD> fill(timg);
+    __builtin_amdgcn_sched_barrier(0);
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t lo = blockIdx.x * per + (blockIdx.x < more ? blockIdx.x : more);
+    const uint32_t hi = lo + per + (blockIdx.x < more);
+    Unit un;
+    un.off = off;
+    un.nbytes = nbytes;
+    un.meta = meta;
+    un.w[0] = (uint32_t)w01;
+    un.w[1] = (uint32_t)(w01 >> 32);
+    un.w[2] = (uint32_t)w23;
+    un.w[3] = (uint32_t)(w23 >> 32);
+    const auto record = [](uint32_t) { return 0; };
+    const auto load = [&](uint32_t i, int, Part<DEC, NB> &p) {
+        p.load(lane, un, lo + i < hi, lo + i, nullptr, sched, n_sched, in);
+    };
+    run_parts<DEC, NB, BD>(lds, fill, hi - lo, in == out, record, load, in, out);
+}
+
+// Waves per workgroup: as few (4, 8 or 16) as hold the parts on n_wg
+// workgroups at once, and a unit's parts.
+static uint32_t short_waves(uint64_t parts, uint32_t n_wg, uint32_t unit_parts) {
+    uint32_t waves = 4;
+    while (waves < 16 && (unit_parts > waves || parts > (uint64_t)waves * n_wg))
+        waves *= 2;
+    return waves;
+}
+
+#define AESGPU_SHORT(KERNEL, K, DEC_, NB_, WAVES_)                                             \
+    ((DEC_) ? ((NB_) == 2      ? (K)&KERNEL<true, 2, 1024>                                     \
+               : (WAVES_) == 4 ? (K)&KERNEL<true, 1, 256>                                      \
+               : (WAVES_) == 8 ? (K)&KERNEL<true, 1, 512>                                      \
+                               : (K)&KERNEL<true, 1, 1024>)                                    \
+            : ((NB_) == 2      ? (K)&KERNEL<false, 2, 1024>                                    \
+               : (WAVES_) == 4 ? (K)&KERNEL<false, 1, 256>                                     \
+               : (WAVES_) == 8 ? (K)&KERNEL<false, 1, 512>                                     \
+                               : (K)&KERNEL<false, 1, 1024>))
+
+bool launch_tiles_short(bool dec, const Unit *d_units, uint32_t n_units, uint32_t max_bytes,
+                        const aes_schedule_t *d_sched, uint32_t n_sched, const uint32_t *d_timg,
+                        const void *d_preds, const uint8_t *d_in, uint8_t *d_out, int n_cu,
+                        void *stream, int *err) {
+    const uint32_t cus = (uint32_t)n_cu < 65535u ? (uint32_t)n_cu : 65535u;
+    // One block per lane for one pass, else two.
+    int nb = 1;
+    uint32_t lg = 0;
+    for (;; nb++) {
+        lg = 0;
+        while (lg < 5 && (uint64_t)max_bytes > ((1024ull * nb) << lg))
+            lg++;
+        if (nb == 2 || ((uint64_t)n_units << lg) <= 16ull * cus)
+            break;
+    }
+    const uint64_t parts = (uint64_t)n_units << lg;
+    if (lg > 4 || parts > SHORT_PARTS_PER_CU * cus)
+        return false;
+    const uint32_t waves = nb == 2 ? 16u : short_waves(parts, cus, 1u << lg);
+    const uint32_t per_wg = waves >> lg;  // units of one pass
+    uint32_t grid = (n_units + per_wg - 1) / per_wg;
+    if (grid > cus)
+        grid = cus;
+    using K = void (*)(const Unit *, uint32_t, uint16_t, uint16_t, const uint32_t *, const aes_schedule_t *,
+                       const uint8_t *, uint32_t, const uint4 *, uint8_t *);
+    const K k = AESGPU_SHORT(k_tiles_short, K, dec, nb, waves);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(64 * waves), 0, (hipStream_t)stream, d_units,
+                       n_units / grid, (uint16_t)(n_units % grid), (uint16_t)lg, d_timg, d_sched, d_in, n_sched, (const uint4 *)d_preds, d_out);
+    *err = hipGetLastError();
+    return true;
+}
+
+bool launch_request_short(const aes_req_t &r, const aes_schedule_t *d_sched, uint32_t n_sched,
+                          const uint32_t *d_timg, const uint8_t *d_in, uint8_t *d_out, int n_cu,
+                          void *stream, int *err) {
+    if (r.op == AES_OP_CBC_ENC)
+        return false;
+    // Decrypted in place with CBC, all parts have to be in one workgroup.
+    const uint32_t n_wg = r.op == AES_OP_CBC_DEC && d_in == d_out ? 1u : (uint32_t)n_cu;
+    const int nb = r.length > 16ull * 1024u * n_wg ? 2 : 1;
+    const uint64_t parts = (r.length + 1024u * nb - 1) / (1024u * nb);
+    if (parts > SHORT_PARTS_PER_CU * (uint64_t)n_wg && n_wg > 1)
+        return false;
+    const uint32_t waves = nb == 2 ? 16u : short_waves(parts, n_wg, 1);
+    uint32_t grid = (uint32_t)((parts + waves - 1) / waves);
+    if (grid > n_wg)
+        grid = n_wg;
+    uint64_t w01 = 0, w23 = 0;
+    if (r.op == AES_OP_CTR) {  // nonce, then the counter as an integer
+        memcpy(&w01, r.iv, 8);
+        for (int i = 8; i < 16; i++)
+            w23 = (w23 << 8) | r.iv[i];
+    } else if (r.op == AES_OP_CBC_DEC) {
+        memcpy(&w01, r.iv, 8);
+        memcpy(&w23, r.iv + 8, 8);
+    }
+    using K = void (*)(const uint32_t *, const aes_schedule_t *, const uint8_t *, uint64_t,
+                       uint32_t, uint32_t, uint32_t, uint32_t, uint64_t, uint64_t, uint32_t,
+                       uint8_t *);
+    const bool dec = r.op == AES_OP_CBC_DEC || r.op == AES_OP_ECB_DEC;
+    const K k = AESGPU_SHORT(k_request_short, K, dec, nb, waves);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(64 * waves), 0, (hipStream_t)stream, d_timg, d_sched,
+                       d_in, r.offset, (uint32_t)r.length, r.key_idx | (r.op << META_OP_SHIFT),
+                       (uint32_t)(parts / grid), (uint32_t)(parts % grid), w01, w23, n_sched, d_out);
+    *err = hipGetLastError();
+    return true;
+}
+#undef AESGPU_SHORT
+
+}  // namespace aesgpu

@@ -80,9 +80,11 @@ struct MixedArgs {
 // Host-side launchers.  Each returns a hipError_t value.  Tile kernels:
 // aes_tiles_ctr.hip and aes_tiles_dec.hip; the others: aes_kernels.hip.
 // Tile launchers take d_ctrs: TILE_CTRS zeroed per-workgroup counters that
-// every launch leaves zeroed (launches sharing them must not overlap).
+// every launch leaves zeroed (launches sharing them must not overlap), and
+// max_bytes, the largest unit's size.
 constexpr uint32_t TILE_CTRS = 65536;
-int launch_ctr_tiles(const Unit *d_units, uint32_t n_units, const aes_schedule_t *d_sched,
+int launch_ctr_tiles(const Unit *d_units, uint32_t n_units, uint32_t max_bytes,
+                     const aes_schedule_t *d_sched,
                      uint32_t n_sched, const uint32_t *d_timg, const uint8_t *d_in,
                      uint8_t *d_out, uint32_t *d_ctrs, const TileLaunch &cfg, int n_cu,
                      void *stream);
@@ -98,7 +100,8 @@ int launch_dec_bitslice(const Unit *d_units, uint32_t n_units, const aes_schedul
                         uint8_t *d_out, void *stream);
 // d_preds: NULL, or one 16-byte predecessor per unit written by
 // launch_snapshot_preds (used for FLAG_PRED_IN units instead of reading d_in).
-int launch_cbcdec_tiles(const Unit *d_units, uint32_t n_units, const aes_schedule_t *d_sched,
+int launch_cbcdec_tiles(const Unit *d_units, uint32_t n_units, uint32_t max_bytes,
+                        const aes_schedule_t *d_sched,
                         uint32_t n_sched, const uint32_t *d_timg, const void *d_preds,
                         const uint8_t *d_in, uint8_t *d_out, uint32_t *d_ctrs,
                         const TileLaunch &cfg, int n_cu, void *stream);
@@ -112,6 +115,23 @@ int launch_mixed(const MixedArgs &a, int nb, int grid, void *stream);
 int launch_request(const aes_req_t &r, uint32_t tile, const aes_schedule_t *d_sched,
                    uint32_t n_sched, const uint32_t *d_timg, const uint8_t *d_in,
                    uint8_t *d_out, int n_cu, void *stream);
+// Units (decryption or encryption tiles) of at most max_bytes each, or one
+// request by value, by the kernels for short launches (aes_tiles_short.hip).
+// False: too much for them, nothing was launched; else *err is the launch's
+// hipError_t.
+// Where the line lies: microseconds a launch of 4 KiB units, here and with the
+// tile kernels (AES-128 CTR; CBC decryption within 1): 1 to 1,024 units 8 and 9
+// to 15 (the launch call itself takes 7.5), 2,048 11.2 and 16.4, 3,000 14.1 and
+// 16.9, 4,096 18.4 and 17.7, 32,768 114 and 93.  In parts of 2 KiB a compute
+// unit, 4,096 such units are 32.
+constexpr uint32_t SHORT_PARTS_PER_CU = 24;
+bool launch_tiles_short(bool dec, const Unit *d_units, uint32_t n_units, uint32_t max_bytes,
+                        const aes_schedule_t *d_sched, uint32_t n_sched, const uint32_t *d_timg,
+                        const void *d_preds, const uint8_t *d_in, uint8_t *d_out, int n_cu,
+                        void *stream, int *err);
+bool launch_request_short(const aes_req_t &r, const aes_schedule_t *d_sched, uint32_t n_sched,
+                          const uint32_t *d_timg, const uint8_t *d_in, uint8_t *d_out, int n_cu,
+                          void *stream, int *err);
 // In-place CBC decryption: copies in[off-16, off) of every FLAG_PRED_IN unit u
 // to d_preds[16u..16u+15] before the tile kernel overwrites those bytes.
 int launch_snapshot_preds(const Unit *d_units, uint32_t n_units, const uint8_t *d_in,
