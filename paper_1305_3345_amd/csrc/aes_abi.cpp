@@ -575,16 +575,41 @@ int launch_planned(aes_ctx *ctx, const PlanView &v, const aes_schedule_t *d_sche
         return AES_OK;
     }
     if ((e = launch_cbcdec_tiles(u_dec, (uint32_t)n_dec, v.max_bytes, d_scheds, n_scheds, ctx->d_timg,
-                                 d_preds, d_in, d_out, v.d_ctrs, ctx->tile_dec, ctx->n_cu,
-                                 stream)))
+                                 d_preds, d_in, d_out, v.d_ctrs, ctx->tile_dec,
+                                 ctx->n_cu, stream)))
         return hip_fail((hipError_t)e);
     if ((e = launch_ctr_tiles(u_ctr, (uint32_t)n_ctr_tab, v.max_bytes, d_scheds, n_scheds, ctx->d_timg, d_in,
-                              d_out, v.d_ctrs + TILE_CTRS, ctx->tile_ctr, ctx->n_cu, stream)))
+                              d_out, v.d_ctrs + TILE_CTRS, ctx->tile_ctr, ctx->n_cu,
+                              stream)))
         return hip_fail((hipError_t)e);
     if ((e = launch_cbcenc_chains(u_chain, (uint32_t)v.n_chain, d_scheds, n_scheds, ctx->d_timg,
                                   d_in, d_out, ctx->chain, ctx->n_cu, stream)))
         return hip_fail((hipError_t)e);
     return AES_OK;
+}
+
+// A few tiles of one side (n_dec or n_enc of them at `units`): launched with
+// the unit table among the kernel's arguments, so that the call takes no
+// staging buffer, copy or event.  False: not such a batch, nothing was launched.
+bool launch_few(aes_ctx *ctx, const Unit *units, size_t n_dec, size_t n_enc, size_t n_chain,
+                bool pred_in, uint32_t max_bytes, const aes_schedule_t *d_scheds,
+                uint32_t n_scheds, const uint8_t *d_in, uint8_t *d_out, void *stream, int *st) {
+    const bool dec = n_dec > 0;
+    if (n_chain || (dec && n_enc) || n_dec + n_enc > INLINE_UNITS || (pred_in && d_in == d_out) ||
+        !is_default(dec ? ctx->tile_dec : ctx->tile_ctr) ||
+        (dec ? ctx->dec_variant != AES_DEC_TABLE : ctx->ctr_variant != AES_CTR_TABLE))
+        return false;
+    const hipError_t e = hipSetDevice(ctx->device);
+    if (e != hipSuccess) {
+        *st = hip_fail(e);
+        return true;
+    }
+    int err = hipSuccess;
+    if (!launch_tiles_inline(dec, units, (uint32_t)(n_dec + n_enc), max_bytes, d_scheds, n_scheds,
+                             ctx->d_timg, d_in, d_out, ctx->n_cu, stream, &err))
+        return false;
+    *st = err == hipSuccess ? AES_OK : hip_fail((hipError_t)err);
+    return true;
 }
 
 void pack_units(const Planned &p, void *dst) {
@@ -617,6 +642,10 @@ int run_batch(aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_scheds,
         return AES_OK;
     if (ctx->device == AES_DEVICE_NONE)
         return AES_ERR_DEVICE;
+    if (launch_few(ctx, p.dec.empty() ? p.ctr.data() : p.dec.data(), p.dec.size(), p.ctr.size(),
+                   p.chains.size(), p.dec_has_pred_in, p.max_tile, d_scheds, n_scheds, d_in, d_out,
+                   stream, &st))
+        return st;
     const size_t ubytes = (p.dec.size() + p.ctr.size() + p.chains.size()) * sizeof(Unit);
     const size_t need = units_bytes(p.dec.size(), p.ctr.size(), p.chains.size());
     Slot *sp = nullptr;
@@ -693,7 +722,7 @@ int run_batch_noalloc(aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_s
     // 1. The per-request rules (as validate), order, and the unit counts.
     const uint32_t tile = ctx->tile_bytes;
     uint64_t n_dec = 0, n_ctr = 0, n_ecb = 0, n_chain = 0, n_live = 0, payload = 0;
-    uint64_t dec_bytes = 0, ctr_bytes = 0, last_off = 0, max_tile = 0;
+    uint64_t dec_bytes = 0, ctr_bytes = 0, last_off = 0;
     bool sorted = true, pred_in = false;
     for (uint64_t i = 0; i < n; i++) {
         const aes_req_t &r = reqs[i];
@@ -709,8 +738,6 @@ int run_batch_noalloc(aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_s
         n_live++;
         payload += r.length;
         const uint64_t t = (r.length + tile - 1) / tile;
-        if (r.op != AES_OP_CBC_ENC)
-            max_tile = std::max<uint64_t>(max_tile, std::min<uint64_t>(tile, r.length));
         if (r.op == AES_OP_CBC_ENC) {
             n_chain++;
         } else if (is_dec_tile_op(r.op)) {
@@ -815,7 +842,7 @@ int run_batch_noalloc(aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_s
     if (e)
         return hip_fail((hipError_t)e);
     const PlanView v{d_scratch, (Unit *)d_scratch + n_units, d_ctrs, (size_t)n_dec, (size_t)(n_ctr + n_ecb), (size_t)n_chain,
-                     pred_in, dec_bytes, ctr_bytes, (uint32_t)max_tile, (size_t)n_ecb};
+                     pred_in, dec_bytes, ctr_bytes, tile, (size_t)n_ecb};
     return launch_planned(ctx, v, d_scheds, n_scheds, d_in, d_out, stream);
 }
 

@@ -362,7 +362,8 @@ __device__ __forceinline__ void chain_row_run(const uint32_t *lds, uint32_t L0, 
         rk[r] = ek[4 * r + (r & 1 ? p : b)];
     // Byte b of a word, at the address position (bits 8..15).
     const auto at8 = [b](uint32_t w) { return ((w >> (8u * b)) & 0xFFu) << 8; };
-    const uint32_t ci = (p + b) & 3u, co = (p - b) & 3u;  // columns of this lane's bytes, in and out
+    // Columns of this lane's bytes, in and out.
+    const uint32_t ci = (p + b) & 3u, co = (p - b) & 3u;
     const uint32_t rko = at8(ek[4 * nr + co]);
     const uint32_t rki = at8(ek[4 * nr + ci]);
     // Round 1's lookup: byte b of column ci through table b.

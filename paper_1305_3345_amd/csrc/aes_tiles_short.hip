@@ -64,6 +64,33 @@ __global__ __launch_bounds__(BD) void k_tiles_short(
     run_parts<DEC, NB, BD>(lds, fill, n_parts, in == out, record, load, in, out);
 }
 
+// A unit table among the kernel arguments.
+struct InlineUnits {
+    Unit u[INLINE_UNITS];
+};
+
+// One pass over the n units of `table`, in workgroups of four waves (parts of
+// 1 KiB, so units of up to 4 KiB, 2^parts_log2 parts each).
+template <bool DEC>
+__global__ __launch_bounds__(256) void k_tiles_inline(
+    const uint32_t *__restrict__ timg, const aes_schedule_t *__restrict__ sched, const uint8_t *in,
+    uint32_t n, uint32_t parts_log2, uint32_t n_sched, uint8_t *out, InlineUnits table) {
+    __shared__ __align__(16) uint32_t lds[DEC ? LDS_DEC_WORDS : LDS_ENC_WORDS];
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t i = __builtin_amdgcn_readfirstlane(blockIdx.x * 4u + (threadIdx.x >> 6));
+    const uint32_t u = i >> parts_log2;
+    const Unit un = table.u[u < n ? u : 0u];
+    __builtin_amdgcn_sched_barrier(0);
+    const TableFill<DEC, 256> fill(timg);
+    __builtin_amdgcn_sched_barrier(0);
+    const auto record = [](uint32_t) { return 0; };
+    const auto load = [&](uint32_t k, int, Part<DEC, 1> &p) {
+        // The only pass; there is no second one to load.
+        p.load(lane, un, u < n && k < 4u, i & ((1u << parts_log2) - 1u), nullptr, sched, n_sched, in);
+    };
+    run_parts<DEC, 1, 256>(lds, fill, 1u, false, record, load, in, out);
+}
+
 // One request as one unit; workgroup g takes the next `per` parts of it, the
 // first `more` workgroups one more.
 template <bool DEC, int NB, uint32_t BD>
@@ -139,6 +166,24 @@ bool launch_tiles_short(bool dec, const Unit *d_units, uint32_t n_units, uint32_
     const K k = AESGPU_SHORT(k_tiles_short, K, dec, nb, waves);
     hipLaunchKernelGGL(k, dim3(grid), dim3(64 * waves), 0, (hipStream_t)stream, d_units,
                        n_units / grid, (uint16_t)(n_units % grid), (uint16_t)lg, d_timg, d_sched, d_in, n_sched, (const uint4 *)d_preds, d_out);
+    *err = hipGetLastError();
+    return true;
+}
+
+bool launch_tiles_inline(bool dec, const Unit *units, uint32_t n_units, uint32_t max_bytes,
+                         const aes_schedule_t *d_sched, uint32_t n_sched, const uint32_t *d_timg,
+                         const uint8_t *d_in, uint8_t *d_out, int n_cu, void *stream, int *err) {
+    uint32_t lg = 0;
+    while (lg < 2 && max_bytes > 1024u << lg)
+        lg++;
+    const uint32_t grid = ((n_units << lg) + 3) / 4;
+    if (n_units > INLINE_UNITS || max_bytes > 1024u << lg || grid > (uint32_t)n_cu)
+        return false;
+    InlineUnits t;
+    memcpy(t.u, units, n_units * sizeof(Unit));
+    hipLaunchKernelGGL(dec ? &k_tiles_inline<true> : &k_tiles_inline<false>, dim3(grid), dim3(256),
+                       0, (hipStream_t)stream, d_timg, d_sched, d_in, n_units, lg, n_sched, d_out,
+                       t);
     *err = hipGetLastError();
     return true;
 }

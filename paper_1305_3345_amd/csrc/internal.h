@@ -44,6 +44,10 @@ struct TileLaunch {
     int grid = 0;           // workgroups; 0 = one per compute unit
 };
 bool tile_shape_supported(int nb, int wg_threads);
+inline bool is_default(const TileLaunch &t) {
+    return t.nb == TileLaunch().nb && t.wg_threads == TileLaunch().wg_threads &&
+           t.grid == TileLaunch().grid;
+}
 
 struct ChainLaunch {
     int wg_threads = 256;
@@ -84,10 +88,9 @@ struct MixedArgs {
 // max_bytes, the largest unit's size.
 constexpr uint32_t TILE_CTRS = 65536;
 int launch_ctr_tiles(const Unit *d_units, uint32_t n_units, uint32_t max_bytes,
-                     const aes_schedule_t *d_sched,
-                     uint32_t n_sched, const uint32_t *d_timg, const uint8_t *d_in,
-                     uint8_t *d_out, uint32_t *d_ctrs, const TileLaunch &cfg, int n_cu,
-                     void *stream);
+                     const aes_schedule_t *d_sched, uint32_t n_sched, const uint32_t *d_timg,
+                     const uint8_t *d_in, uint8_t *d_out, uint32_t *d_ctrs,
+                     const TileLaunch &cfg, int n_cu, void *stream);
 // Bitsliced CTR (aes_bitslice.hip): units in groups of 8 per wave, worked in
 // 4 KiB chunks; a group whose units share a key makes one pass per chunk.
 int launch_ctr_bitslice(const Unit *d_units, uint32_t n_units, const aes_schedule_t *d_sched,
@@ -101,10 +104,10 @@ int launch_dec_bitslice(const Unit *d_units, uint32_t n_units, const aes_schedul
 // d_preds: NULL, or one 16-byte predecessor per unit written by
 // launch_snapshot_preds (used for FLAG_PRED_IN units instead of reading d_in).
 int launch_cbcdec_tiles(const Unit *d_units, uint32_t n_units, uint32_t max_bytes,
-                        const aes_schedule_t *d_sched,
-                        uint32_t n_sched, const uint32_t *d_timg, const void *d_preds,
-                        const uint8_t *d_in, uint8_t *d_out, uint32_t *d_ctrs,
-                        const TileLaunch &cfg, int n_cu, void *stream);
+                        const aes_schedule_t *d_sched, uint32_t n_sched, const uint32_t *d_timg,
+                        const void *d_preds, const uint8_t *d_in, uint8_t *d_out,
+                        uint32_t *d_ctrs, const TileLaunch &cfg, int n_cu,
+                        void *stream);
 int launch_cbcenc_chains(const Unit *d_units, uint32_t n_units, const aes_schedule_t *d_sched,
                          uint32_t n_sched, const uint32_t *d_timg, const uint8_t *d_in,
                          uint8_t *d_out, const ChainLaunch &cfg, int n_cu, void *stream);
@@ -129,6 +132,13 @@ bool launch_tiles_short(bool dec, const Unit *d_units, uint32_t n_units, uint32_
                         const aes_schedule_t *d_sched, uint32_t n_sched, const uint32_t *d_timg,
                         const void *d_preds, const uint8_t *d_in, uint8_t *d_out, int n_cu,
                         void *stream, int *err);
+// The same for a table in host memory of up to INLINE_UNITS units (none with
+// FLAG_PRED_IN if d_in == d_out), copied into the kernel's arguments: nothing
+// of it is read after the call.
+constexpr uint32_t INLINE_UNITS = 32;
+bool launch_tiles_inline(bool dec, const Unit *units, uint32_t n_units, uint32_t max_bytes,
+                         const aes_schedule_t *d_sched, uint32_t n_sched, const uint32_t *d_timg,
+                         const uint8_t *d_in, uint8_t *d_out, int n_cu, void *stream, int *err);
 bool launch_request_short(const aes_req_t &r, const aes_schedule_t *d_sched, uint32_t n_sched,
                           const uint32_t *d_timg, const uint8_t *d_in, uint8_t *d_out, int n_cu,
                           void *stream, int *err);

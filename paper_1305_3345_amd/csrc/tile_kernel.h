@@ -25,8 +25,9 @@ constexpr uint32_t TILE_SPREAD_GRID = TILE_CTRS / TILE_CTR_STRIDE;
 
 // One table set in LDS per workgroup.  Workgroup g owns a contiguous range
 // of units: `per` of them, the first `more` workgroups one more (quotient and
-// remainder come from the host, a division here is about 200 instructions).  Wave w starts on unit w of the range without a claim (its record
-// is loaded, and its first claim issued, while the tables fill); after that,
+// remainder come from the host, a division here is about 200 instructions).
+// Wave w starts on unit w of the range without a claim (its record is loaded,
+// and its first claim issued, while the tables fill); after that,
 // waves claim units wpb, wpb + 1, ... of the range one at a time from the
 // workgroup's counter in wg_ctr.  The SIMD arbiter runs the oldest wave first,
 // so with a fixed share per wave the first waves of each SIMD finished in
@@ -41,7 +42,8 @@ constexpr uint32_t TILE_SPREAD_GRID = TILE_CTRS / TILE_CTR_STRIDE;
 // it).
 template <bool DEC, int NB, int WG>
 __global__ __launch_bounds__(WG) void k_tiles(const Unit *__restrict__ units, uint32_t per,
-                                              uint32_t more, const aes_schedule_t *__restrict__ sched,
+                                              uint32_t more,
+                                              const aes_schedule_t *__restrict__ sched,
                                               uint32_t n_sched, const uint32_t *__restrict__ timg,
                                               const uint4 *__restrict__ preds, const uint8_t *in,
                                               uint8_t *out, uint32_t *__restrict__ wg_ctr) {
@@ -105,18 +107,18 @@ inline TileKernel pick_tile_kernel(int nb, int wg) {
 // d_ctrs: TILE_MAX_GRID zeroed counters (zero again after every launch).
 template <bool DEC>
 inline int launch_tiles(const Unit *d_units, uint32_t n_units, uint32_t max_bytes,
-                        const aes_schedule_t *d_sched, uint32_t n_sched, const uint32_t *d_timg, const void *d_preds,
-                        const uint8_t *d_in, uint8_t *d_out, uint32_t *d_ctrs,
-                        const TileLaunch &cfg, int n_cu, void *stream) {
+                        const aes_schedule_t *d_sched, uint32_t n_sched, const uint32_t *d_timg,
+                        const void *d_preds, const uint8_t *d_in, uint8_t *d_out,
+                        uint32_t *d_ctrs, const TileLaunch &cfg, int n_cu,
+                        void *stream) {
     if (!n_units)
         return hipSuccess;
     // Under the default shape, launches of a few passes take the kernel for
     // them; a shape or grid that was set is kept.
-    const TileLaunch plain;
     int err;
-    if (cfg.nb == plain.nb && cfg.wg_threads == plain.wg_threads && cfg.grid == plain.grid &&
-        launch_tiles_short(DEC, d_units, n_units, max_bytes, d_sched, n_sched, d_timg, d_preds, d_in,
-                        d_out, n_cu, stream, &err))
+    if (is_default(cfg) &&
+        launch_tiles_short(DEC, d_units, n_units, max_bytes, d_sched, n_sched, d_timg, d_preds,
+                           d_in, d_out, n_cu, stream, &err))
         return err;
     const TileKernel k = pick_tile_kernel<DEC>(cfg.nb, cfg.wg_threads);
     if (!k)
@@ -131,8 +133,8 @@ inline int launch_tiles(const Unit *d_units, uint32_t n_units, uint32_t max_byte
     if (!d_ctrs || (uint32_t)grid > TILE_MAX_GRID)
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(k, dim3(grid), dim3(cfg.wg_threads), 0, (hipStream_t)stream, d_units,
-                       n_units / grid, n_units % grid, d_sched, n_sched, d_timg, (const uint4 *)d_preds, d_in, d_out,
-                       d_ctrs);
+                       n_units / grid, n_units % grid, d_sched, n_sched, d_timg,
+                       (const uint4 *)d_preds, d_in, d_out, d_ctrs);
     return hipGetLastError();
 }
 

@@ -111,3 +111,23 @@ def test_requests_by_value(ctx, op, inplace):
         torch.cuda.synchronize()
         msg = first_mismatch(d_out.cpu().numpy(), run_oracle(wl, inp, inplace=inplace))
         assert msg is None, f"{length}: {msg}"
+
+
+@pytest.mark.parametrize("inplace", [False, True])
+@pytest.mark.parametrize("op", list(OPS))
+@pytest.mark.parametrize("n", [1, 31, 32, 33])
+def test_units_among_arguments(fresh, op, n, inplace):
+    """Calls of up to 32 units, whose table travels among the kernel's
+    arguments, and the first beyond: whole and ragged units up to 4 KiB, and
+    two calls in a row with other requests."""
+    print(f"[gpu] inline units: {op}, {n} units, inplace={inplace}", flush=True)
+    for seed in (n, n + 100):
+        lengths = np.random.default_rng(seed).integers(1, 257, n) * 16
+        if op == "ctr":
+            lengths[-1] -= 7
+        wl = requests(op, lengths, seed)
+        inp = wl.data()
+        for form in ("single", "batch"):
+            msg = first_mismatch(run_gpu(fresh, wl, inp, form=form, inplace=inplace),
+                                 run_oracle(wl, inp, inplace=inplace))
+            assert msg is None, f"{form}: {msg}"
