@@ -367,14 +367,17 @@ int aes_request_launches(aes_ctx_t *ctx, const aes_schedule_t *d_scheds, uint32_
                          const uint8_t *d_in, uint8_t *d_out, uint64_t buf_bytes,
                          const aes_req_t *reqs, uint64_t n_reqs, void *stream);
 
-/* An instantiated HIP graph owned by the library. */
+/* Recorded launches owned by the library: an instantiated HIP graph, or, where
+ * there are few, the launches themselves (a plan's kernels; up to four
+ * requests), which replay faster one by one. */
 typedef struct aes_graph aes_graph_t;
 
-/* Captures one launch of a plan (with these buffers) into a graph; its
- * replays count as launches of the plan (they must not overlap them). */
+/* Records one launch of a plan (with these buffers and the context's launch
+ * configuration as it is now) as a graph; its replays count as launches of the
+ * plan (they must not overlap them). */
 int aes_plan_graph(aes_plan_t *plan, const aes_schedule_t *d_scheds, const uint8_t *d_in,
                    uint8_t *d_out, aes_graph_t **out);
-/* Captures n_reqs per-request launches (aes_request_launch) into one graph. */
+/* Records n_reqs per-request launches (aes_request_launch) as one graph. */
 int aes_requests_graph(aes_ctx_t *ctx, const aes_schedule_t *d_scheds, uint32_t n_scheds,
                        const uint8_t *d_in, uint8_t *d_out, uint64_t buf_bytes,
                        const aes_req_t *reqs, uint64_t n_reqs, aes_graph_t **out);

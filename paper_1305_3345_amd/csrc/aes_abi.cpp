@@ -314,15 +314,11 @@ struct Slot {
     uint32_t *d_ctrs = nullptr;   // tile-kernel counters: decryption side, then encryption
 };
 
-struct aes_ctx {
+// What a launch reads of its context: the device and the launch configuration.
+struct LaunchCtx {
     int device = AES_DEVICE_NONE;
     int n_cu = 0;
-    char arch[32] = "host";  // device architecture (gcnArchName up to ':'), for the tune cache
     uint32_t *d_timg = nullptr;
-    static constexpr int N_SLOTS = 4;
-    Slot slots[N_SLOTS];
-    int next_slot = 0;
-    uint32_t tile_bytes = DEFAULT_TILE;
     TileLaunch tile_ctr;
     TileLaunch tile_dec;
     ChainLaunch chain{256, 64, true, 0};  // several lanes per chain
@@ -331,6 +327,14 @@ struct aes_ctx {
     int grid = 0;            // tile / fused kernel workgroups, 0 = one per compute unit
     uint32_t ctr_variant = AES_CTR_TABLE;
     uint32_t dec_variant = AES_DEC_TABLE;
+};
+
+struct aes_ctx : LaunchCtx {
+    char arch[32] = "host";  // device architecture (gcnArchName up to ':'), for the tune cache
+    static constexpr int N_SLOTS = 4;
+    Slot slots[N_SLOTS];
+    int next_slot = 0;
+    uint32_t tile_bytes = DEFAULT_TILE;
     hipStream_t capture = nullptr;  // private stream for graph capture and tuning
     // Scratch of the single-call forms, reused from call to call (a context
     // is used by one thread at a time): requests built from the caller's
@@ -339,13 +343,6 @@ struct aes_ctx {
     Planned scratch_plan;
     std::unique_ptr<HostPool> pool;  // large single-op calls (created on first use)
     hipStream_t copy = nullptr;      // unit-table uploads of the single-call forms
-};
-
-struct aes_graph {
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    int device = 0;
-    uint64_t n_nodes = 0;
 };
 
 struct aes_plan {
@@ -392,6 +389,35 @@ PlanView view_of(const Planned &p, const void *units, void *d_units, uint32_t *d
                     d_ctrs, p.dec.size(), p.ctr.size(), p.chains.size(), p.dec_has_pred_in,
                     p.dec_bytes, p.ctr_bytes, p.max_tile, p.n_ecb};
 }
+
+}  // namespace
+
+// A recorded plan launch, a few recorded request launches, or a HIP graph of
+// many.  Few launches are replayed as launches: hipGraphLaunch costs the host
+// about 15 us whatever it holds and the device about 6 us around the nodes
+// (one request: 15.4 us a replay against 4.0; four: 21.1 against 15.7; a plan
+// of two kernels: 38.6 against 31.9), while from eight launches on the graph
+// takes less of the host (16.6 us against 25.7) for the same GPU time.
+struct aes_graph {
+    int device = 0;
+    hipGraph_t graph = nullptr;
+    hipGraphExec_t exec = nullptr;
+    // As captured: the context's configuration, buffers, and either a plan's
+    // view or the requests with their tile sizes.
+    LaunchCtx cfg;
+    const aes_schedule_t *d_scheds = nullptr;
+    uint32_t n_scheds = 0;
+    const uint8_t *d_in = nullptr;
+    uint8_t *d_out = nullptr;
+    bool has_plan = false;
+    PlanView view{};
+    static constexpr uint64_t MAX_DIRECT = 4;
+    uint64_t n_reqs = 0;
+    aes_req_t reqs[MAX_DIRECT];
+    uint32_t tiles[MAX_DIRECT];
+};
+
+namespace {
 
 // Zeroed tile-kernel counters for one plan or staging slot (the kernels
 // leave them zeroed after every launch).
@@ -508,7 +534,7 @@ uint32_t dec_workgroups(const PlanView &v, int grid) {
 }
 
 // Launches the kernels of one planned batch whose unit table is at v.d_units.
-int launch_planned(aes_ctx *ctx, const PlanView &v, const aes_schedule_t *d_scheds,
+int launch_planned(const LaunchCtx *ctx, const PlanView &v, const aes_schedule_t *d_scheds,
                    uint32_t n_scheds, const uint8_t *d_in, uint8_t *d_out, void *stream) {
     const Unit *u_dec = (const Unit *)v.d_units;
     const Unit *u_ctr = u_dec + v.n_dec;
@@ -1412,6 +1438,18 @@ int aes_ctx_set_config(aes_ctx_t *ctx, const aes_launch_config_t *cfg) {
 
 // ---------------------------------------------------- one request, one launch
 
+namespace {
+
+// Bytes per unit of a request's own launch.  In place, a multi-tile CBC
+// decryption stays in one wave, which carries each predecessor block in
+// registers before overwriting it.
+uint32_t request_tile(const aes_ctx *ctx, const aes_req_t &r, bool in_place) {
+    return r.op == AES_OP_CBC_DEC && in_place && r.length > ctx->tile_bytes ? (uint32_t)r.length
+                                                                            : ctx->tile_bytes;
+}
+
+}  // namespace
+
 int aes_request_launch(aes_ctx_t *ctx, const aes_schedule_t *d_scheds, uint32_t n_scheds,
                        const uint8_t *d_in, uint8_t *d_out, uint64_t buf_bytes,
                        const aes_req_t *req, void *stream) {
@@ -1427,12 +1465,7 @@ int aes_request_launch(aes_ctx_t *ctx, const aes_schedule_t *d_scheds, uint32_t 
     if (ctx->device == AES_DEVICE_NONE)
         return AES_ERR_DEVICE;
     HIP_TRY(hipSetDevice(ctx->device));
-    // In place, a multi-tile CBC decryption stays in one wave, which carries
-    // each predecessor block in registers before overwriting it.
-    uint32_t tile = ctx->tile_bytes;
-    if (req->op == AES_OP_CBC_DEC && d_in == d_out && req->length > tile)
-        tile = (uint32_t)req->length;
-    const int e = launch_request(*req, tile, d_scheds, n_scheds, ctx->d_timg, d_in, d_out,
+    const int e = launch_request(*req, request_tile(ctx, *req, d_in == d_out), d_scheds, n_scheds, ctx->d_timg, d_in, d_out,
                                  ctx->n_cu, stream);
     if (e)
         return hip_fail((hipError_t)e);
@@ -1465,32 +1498,19 @@ int capture_stream(aes_ctx *ctx) {
     return AES_OK;
 }
 
-// Ends a capture on ctx->capture and instantiates it into *out.
-int finish_capture(aes_ctx *ctx, int launch_status, uint64_t nodes, aes_graph_t **out) {
-    hipGraph_t g = nullptr;
-    hipError_t e = hipStreamEndCapture(ctx->capture, &g);
-    if (launch_status) {
-        if (g)
-            (void)hipGraphDestroy(g);
-        return launch_status;
-    }
-    if (e != hipSuccess)
-        return hip_fail(e);
-    aes_graph *gr = new (std::nothrow) aes_graph();
-    if (!gr) {
-        (void)hipGraphDestroy(g);
-        return AES_ERR_NOMEM;
-    }
-    gr->graph = g;
-    gr->device = ctx->device;
-    gr->n_nodes = nodes;
-    if ((e = hipGraphInstantiate(&gr->exec, g, nullptr, nullptr, 0)) != hipSuccess) {
-        (void)hipGraphDestroy(g);
-        delete gr;
-        return hip_fail(e);
-    }
-    *out = gr;
-    return AES_OK;
+// A graph record of launches on the context's device over these buffers.
+aes_graph *new_graph(const aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_scheds,
+                     const uint8_t *d_in, uint8_t *d_out) {
+    aes_graph *g = new (std::nothrow) aes_graph();
+    if (!g)
+        return nullptr;
+    g->device = ctx->device;
+    g->cfg = *ctx;
+    g->d_scheds = d_scheds;
+    g->n_scheds = n_scheds;
+    g->d_in = d_in;
+    g->d_out = d_out;
+    return g;
 }
 
 }  // namespace
@@ -1507,14 +1527,13 @@ int aes_plan_graph(aes_plan_t *plan, const aes_schedule_t *d_scheds, const uint8
         return st;
     if (ctx->device == AES_DEVICE_NONE)
         return AES_ERR_DEVICE;
-    HIP_TRY(hipSetDevice(ctx->device));
-    if ((st = capture_stream(ctx)))
-        return st;
-    HIP_TRY(hipStreamBeginCapture(ctx->capture, hipStreamCaptureModeThreadLocal));
-    st = plan->p.payload ? launch_planned(ctx, view_of(plan->p, plan->d_units, plan->d_units, plan->d_ctrs), d_scheds,
-                                          plan->n_scheds, d_in, d_out, ctx->capture)
-                         : AES_OK;
-    return finish_capture(ctx, st, 1, out);
+    aes_graph *g = new_graph(ctx, d_scheds, plan->n_scheds, d_in, d_out);
+    if (!g)
+        return AES_ERR_NOMEM;
+    g->has_plan = plan->p.payload != 0;
+    g->view = view_of(plan->p, plan->d_units, plan->d_units, plan->d_ctrs);
+    *out = g;
+    return AES_OK;
 }
 
 int aes_requests_graph(aes_ctx_t *ctx, const aes_schedule_t *d_scheds, uint32_t n_scheds,
@@ -1531,25 +1550,64 @@ int aes_requests_graph(aes_ctx_t *ctx, const aes_schedule_t *d_scheds, uint32_t 
     if (ctx->device == AES_DEVICE_NONE)
         return AES_ERR_DEVICE;
     HIP_TRY(hipSetDevice(ctx->device));
-    if ((st = capture_stream(ctx)))
-        return st;
-    HIP_TRY(hipStreamBeginCapture(ctx->capture, hipStreamCaptureModeThreadLocal));
-    uint64_t nodes = 0;
-    for (uint64_t i = 0; i < n_reqs && !st; i++) {
-        if (!reqs[i].length)
-            continue;
-        st = aes_request_launch(ctx, d_scheds, n_scheds, d_in, d_out, buf_bytes, &reqs[i],
-                                ctx->capture);
-        nodes++;
+    aes_graph *g = new_graph(ctx, d_scheds, n_scheds, d_in, d_out);
+    if (!g)
+        return AES_ERR_NOMEM;
+    uint64_t live = 0;
+    for (uint64_t i = 0; i < n_reqs; i++)
+        live += reqs[i].length != 0;
+    if (live <= aes_graph::MAX_DIRECT) {
+        for (uint64_t i = 0; i < n_reqs; i++) {
+            if (!reqs[i].length)
+                continue;
+            g->reqs[g->n_reqs] = reqs[i];
+            g->tiles[g->n_reqs++] = request_tile(ctx, reqs[i], d_in == d_out);
+        }
+        *out = g;
+        return AES_OK;
     }
-    return finish_capture(ctx, st, nodes, out);
+    if ((st = capture_stream(ctx))) {
+        aes_graph_destroy(g);
+        return st;
+    }
+    hipError_t e = hipStreamBeginCapture(ctx->capture, hipStreamCaptureModeThreadLocal);
+    if (e == hipSuccess) {
+        for (uint64_t i = 0; i < n_reqs && !st; i++) {
+            if (reqs[i].length)
+                st = aes_request_launch(ctx, d_scheds, n_scheds, d_in, d_out, buf_bytes, &reqs[i],
+                                        ctx->capture);
+        }
+        e = hipStreamEndCapture(ctx->capture, &g->graph);
+        if (!st && e == hipSuccess)
+            e = hipGraphInstantiate(&g->exec, g->graph, nullptr, nullptr, 0);
+    }
+    if (!st && e != hipSuccess)
+        st = hip_fail(e);
+    if (st) {
+        aes_graph_destroy(g);
+        return st;
+    }
+    *out = g;
+    return AES_OK;
 }
 
 int aes_graph_launch(aes_graph_t *g, void *stream) {
     if (!g)
         return AES_ERR_ARG;
     HIP_TRY(hipSetDevice(g->device));
-    HIP_TRY(hipGraphLaunch(g->exec, (hipStream_t)stream));
+    if (g->exec) {
+        HIP_TRY(hipGraphLaunch(g->exec, (hipStream_t)stream));
+        return AES_OK;
+    }
+    if (g->has_plan)
+        return launch_planned(&g->cfg, g->view, g->d_scheds, g->n_scheds, g->d_in, g->d_out,
+                              stream);
+    for (uint64_t i = 0; i < g->n_reqs; i++) {
+        const int e = launch_request(g->reqs[i], g->tiles[i], g->d_scheds, g->n_scheds,
+                                     g->cfg.d_timg, g->d_in, g->d_out, g->cfg.n_cu, stream);
+        if (e)
+            return hip_fail((hipError_t)e);
+    }
     return AES_OK;
 }
 
