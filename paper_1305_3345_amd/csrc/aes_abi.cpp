@@ -115,6 +115,77 @@ int validate(const aes_req_t *reqs, uint64_t n, uint32_t n_scheds, uint64_t buf_
     return AES_OK;
 }
 
+bool is_dec_tile_op(uint32_t op) { return op == AES_OP_CBC_DEC || op == AES_OP_ECB_DEC; }
+bool is_enc_tile_op(uint32_t op) { return op == AES_OP_CTR || op == AES_OP_ECB_ENC; }
+
+// What one pass over a request list finds: tiles (for CBC encryption: chains)
+// and bytes by operation, and whether the nonempty requests come in offset
+// order without overlapping.
+struct BatchScan {
+    uint64_t units[5] = {0, 0, 0, 0, 0}, bytes[5] = {0, 0, 0, 0, 0};
+    uint64_t longest = 0;  // bytes of the longest request with tiles
+    bool sorted = true, overlap = false, pred_in = false;
+    uint64_t n_dec() const { return units[AES_OP_CBC_DEC] + units[AES_OP_ECB_DEC]; }
+    uint64_t n_enc() const { return units[AES_OP_CTR] + units[AES_OP_ECB_ENC]; }
+    uint64_t n_chain() const { return units[AES_OP_CBC_ENC]; }
+    uint64_t n_units() const { return n_dec() + n_enc() + n_chain(); }
+    uint64_t dec_bytes() const { return bytes[AES_OP_CBC_DEC] + bytes[AES_OP_ECB_DEC]; }
+    uint64_t enc_bytes() const { return bytes[AES_OP_CTR] + bytes[AES_OP_ECB_ENC]; }
+};
+
+inline uint64_t tile_count(uint64_t len, uint32_t tile) {
+    return len <= tile ? 1 : (len + tile - 1) / tile;  // most requests: no division
+}
+
+// The per-request rules of validate, in its order of errors.
+int scan_requests(const aes_req_t *reqs, uint64_t n, uint32_t n_scheds, uint64_t buf_bytes,
+                  uint32_t tile, BatchScan &b) {
+    uint64_t last_off = 0, end = 0, longest = 0;
+    bool sorted = true, overlap = false, pred_in = false;
+    for (uint64_t i = 0; i < n; i++) {
+        const aes_req_t &r = reqs[i];
+        if (r.op > AES_OP_ECB_DEC)
+            return AES_ERR_ARG;
+        const int st = check_request(r.op, r.offset, r.length, r.key_idx, n_scheds, buf_bytes);
+        if (st)
+            return st;
+        if (!r.length)
+            continue;
+        sorted &= r.offset >= last_off;
+        overlap |= r.offset < end;
+        last_off = r.offset;
+        end = r.offset + r.length;
+        b.bytes[r.op] += r.length;
+        if (r.op == AES_OP_CBC_ENC) {
+            b.units[r.op]++;
+            continue;
+        }
+        longest = std::max(longest, r.length);
+        const uint64_t t = tile_count(r.length, tile);
+        b.units[r.op] += t;
+        pred_in |= r.op == AES_OP_CBC_DEC && t > 1;
+    }
+    b.longest = longest;
+    b.sorted = sorted;
+    b.overlap = overlap;
+    b.pred_in = pred_in;
+    return AES_OK;
+}
+
+// The disjointness rule for a list that is not in offset order; ranges has
+// room for every nonempty request.
+int check_disjoint(const aes_req_t *reqs, uint64_t n, std::pair<uint64_t, uint64_t> *ranges) {
+    uint64_t k = 0;
+    for (uint64_t i = 0; i < n; i++)
+        if (reqs[i].length)
+            ranges[k++] = {reqs[i].offset, reqs[i].offset + reqs[i].length};
+    std::sort(ranges, ranges + k);
+    for (uint64_t i = 1; i < k; i++)
+        if (ranges[i].first < ranges[i - 1].second)
+            return AES_ERR_OVERLAP;
+    return AES_OK;
+}
+
 int check_buffers(const uint8_t *d_in, const uint8_t *d_out, uint64_t buf_bytes, uint64_t n,
                   const void *d_scheds) {
     if (!n)
@@ -132,14 +203,15 @@ int check_buffers(const uint8_t *d_in, const uint8_t *d_out, uint64_t buf_bytes,
 // ---------------------------------------------------------------- planner
 
 inline uint32_t le32(const uint8_t *p) {
-    return (uint32_t)p[0] | ((uint32_t)p[1] << 8) | ((uint32_t)p[2] << 16) | ((uint32_t)p[3] << 24);
+    uint32_t v;
+    memcpy(&v, p, 4);
+    return v;
 }
 
 inline uint64_t be64(const uint8_t *p) {
-    uint64_t v = 0;
-    for (int i = 0; i < 8; i++)
-        v = (v << 8) | p[i];
-    return v;
+    uint64_t v;
+    memcpy(&v, p, 8);
+    return __builtin_bswap64(v);
 }
 
 struct Planned {
@@ -170,9 +242,6 @@ struct Planned {
     }
 };
 
-bool is_dec_tile_op(uint32_t op) { return op == AES_OP_CBC_DEC || op == AES_OP_ECB_DEC; }
-bool is_enc_tile_op(uint32_t op) { return op == AES_OP_CTR || op == AES_OP_ECB_ENC; }
-
 // Stable grouping of tiles by key index.  A counting sort over the key
 // indices in use (one pass to count, one to place; buf is scratch) when they
 // are dense enough, else a stable sort.
@@ -196,6 +265,79 @@ void group_by_key(std::vector<Unit> &t, std::vector<Unit> &buf) {
     for (const Unit &u : t)
         buf[start[u.meta & META_KEY_MASK]++] = u;
     t.swap(buf);
+}
+
+// The units of one nonempty request, written from u on; returns the end.
+inline Unit *write_request(uint32_t op, uint64_t off, uint64_t len, uint32_t key,
+                           const uint8_t *iv, uint32_t tile, Unit *u) {
+    const uint32_t meta = key | (op << META_OP_SHIFT);
+    if (op == AES_OP_CTR) {
+        const uint32_t n0 = le32(iv), n1 = le32(iv + 4);
+        uint64_t c = be64(iv + 8);  // mod 2^64, nonce untouched
+        for (;; u++) {
+            u->off = off;
+            u->nbytes = (uint32_t)std::min<uint64_t>(tile, len);
+            u->meta = meta;
+            u->w[0] = n0;
+            u->w[1] = n1;
+            u->w[2] = (uint32_t)c;
+            u->w[3] = (uint32_t)(c >> 32);
+            if (len <= tile)
+                return u + 1;
+            off += tile;
+            len -= tile;
+            c += tile / 16;
+        }
+    }
+    u->off = off;
+    u->meta = meta;
+    if (op == AES_OP_CBC_ENC || op == AES_OP_CBC_DEC)
+        memcpy(u->w, iv, 16);
+    else
+        memset(u->w, 0, 16);  // every block on its own
+    if (op == AES_OP_CBC_ENC) {
+        u->nbytes = (uint32_t)len;
+        return u + 1;
+    }
+    u->nbytes = (uint32_t)std::min<uint64_t>(tile, len);
+    u++;
+    const uint32_t next = meta | (op == AES_OP_CBC_DEC ? FLAG_PRED_IN : 0u);
+    while (len > tile) {
+        off += tile;
+        len -= tile;
+        u->off = off;
+        u->nbytes = (uint32_t)std::min<uint64_t>(tile, len);
+        u->meta = next;
+        memset(u->w, 0, 16);
+        u++;
+    }
+    return u;
+}
+
+// The unit table of a scanned request list: [CBC- and ECB-decrypt tiles | CTR
+// tiles | ECB-encrypt tiles | chains], tiles in request order, chains longest
+// first (equal lengths by key index, then offset): see plan_units.
+void write_units(const aes_req_t *reqs, uint64_t n, uint32_t tile, const BatchScan &b, Unit *u) {
+    Unit *const chains = u + b.n_dec() + b.n_enc();
+    Unit *dec = u, *ctr = dec + b.n_dec(), *ecb = ctr + b.units[AES_OP_CTR], *chain = chains;
+    for (uint64_t i = 0; i < n; i++) {
+        const aes_req_t &r = reqs[i];
+        if (!r.length)
+            continue;
+        Unit *&w = r.op == AES_OP_CTR       ? ctr
+                   : r.op == AES_OP_CBC_ENC ? chain
+                   : r.op == AES_OP_ECB_ENC ? ecb
+                                            : dec;
+        w = write_request(r.op, r.offset, r.length, r.key_idx, r.iv, tile, w);
+    }
+    const auto before = [](const Unit &a, const Unit &c) {
+        const uint32_t ka = a.meta & META_KEY_MASK, kc = c.meta & META_KEY_MASK;
+        if (a.nbytes != c.nbytes)
+            return a.nbytes > c.nbytes;
+        return ka != kc ? ka < kc : a.off < c.off;
+    };
+    if (!std::is_sorted(chains, chain, before))
+        std::sort(chains, chain, before);
 }
 
 // Cuts every request into units: CTR, ECB and CBC-decrypt into tile_bytes
@@ -233,47 +375,18 @@ int plan_units(const aes_req_t *reqs, uint64_t n, uint32_t tile_bytes, bool grou
             p.extent = std::max(p.extent, r.offset + r.length);
             (r.op == AES_OP_CBC_ENC ? p.chain_bytes
                                     : is_enc_tile_op(r.op) ? p.ctr_bytes : p.dec_bytes) += r.length;
-            const uint32_t meta_base = r.key_idx | (r.op << META_OP_SHIFT);
-            if (r.op == AES_OP_CBC_ENC) {
-                Unit u;
-                u.off = r.offset;
-                u.nbytes = (uint32_t)r.length;
-                u.meta = meta_base;
-                for (int w = 0; w < 4; w++)
-                    u.w[w] = le32(r.iv + 4 * w);
-                p.chains.push_back(u);
-                continue;
-            }
-            const uint64_t ctr0 = be64(r.iv + 8);
-            p.max_tile = (uint32_t)std::max<uint64_t>(
-                p.max_tile, std::min<uint64_t>(tile_bytes, r.length));
-            for (uint64_t pos = 0; pos < r.length; pos += tile_bytes) {
-                Unit u;
-                u.off = r.offset + pos;
-                u.nbytes = (uint32_t)std::min<uint64_t>(tile_bytes, r.length - pos);
-                u.meta = meta_base;
-                if (r.op == AES_OP_CTR) {
-                    const uint64_t c = ctr0 + pos / 16;  // mod 2^64, nonce untouched
-                    u.w[0] = le32(r.iv);
-                    u.w[1] = le32(r.iv + 4);
-                    u.w[2] = (uint32_t)c;
-                    u.w[3] = (uint32_t)(c >> 32);
-                    p.ctr.push_back(u);
-                } else if (r.op == AES_OP_ECB_ENC || r.op == AES_OP_ECB_DEC) {
-                    u.w[0] = u.w[1] = u.w[2] = u.w[3] = 0;  // every block on its own
-                    (r.op == AES_OP_ECB_ENC ? p.ecb : p.dec).push_back(u);
-                } else {
-                    if (pos == 0) {
-                        for (int w = 0; w < 4; w++)
-                            u.w[w] = le32(r.iv + 4 * w);
-                    } else {
-                        u.meta |= FLAG_PRED_IN;
-                        u.w[0] = u.w[1] = u.w[2] = u.w[3] = 0;
-                        p.dec_has_pred_in = true;
-                    }
-                    p.dec.push_back(u);
-                }
-            }
+            std::vector<Unit> &v = r.op == AES_OP_CBC_ENC    ? p.chains
+                                   : r.op == AES_OP_CTR     ? p.ctr
+                                   : r.op == AES_OP_ECB_ENC ? p.ecb
+                                                            : p.dec;
+            const uint64_t t = r.op == AES_OP_CBC_ENC ? 1 : tile_count(r.length, tile_bytes);
+            if (r.op != AES_OP_CBC_ENC)
+                p.max_tile = (uint32_t)std::max<uint64_t>(
+                    p.max_tile, std::min<uint64_t>(tile_bytes, r.length));
+            p.dec_has_pred_in |= r.op == AES_OP_CBC_DEC && t > 1;
+            const size_t at = v.size();
+            v.resize(at + t);
+            write_request(r.op, r.offset, r.length, r.key_idx, r.iv, tile_bytes, v.data() + at);
         }
         if (group_ctr) {
             group_by_key(p.ctr, p.sort_buf);
@@ -380,6 +493,7 @@ struct PlanView {
     uint64_t dec_bytes, ctr_bytes;
     uint32_t max_bytes;  // no tile is larger
     size_t n_ecb;  // ECB-encrypt tiles: the last n_ecb of the n_ctr encryption tiles
+    bool zero_ctrs;  // the counters may not be zero: clear what a launch uses first
 };
 
 // units: the table to launch from, d_units: the device allocation (its
@@ -387,7 +501,7 @@ struct PlanView {
 PlanView view_of(const Planned &p, const void *units, void *d_units, uint32_t *d_ctrs) {
     return PlanView{units, (Unit *)d_units + (p.dec.size() + p.ctr.size() + p.chains.size()),
                     d_ctrs, p.dec.size(), p.ctr.size(), p.chains.size(), p.dec_has_pred_in,
-                    p.dec_bytes, p.ctr_bytes, p.max_tile, p.n_ecb};
+                    p.dec_bytes, p.ctr_bytes, p.max_tile, p.n_ecb, false};
 }
 
 }  // namespace
@@ -438,12 +552,13 @@ int alloc_tile_ctrs(uint32_t **out) {
 
 // Unit tables of up to this size are read by the kernels straight from the
 // pinned staging buffer, larger ones are uploaded.  An upload costs the host a
-// copy, an event and a wait (about 15 us a call, one 4 KiB request: 27.7 us a
-// call uploaded, 14.9 us read in place); reading in place costs the kernel the
-// link's latency and bandwidth (one unit 0.5 us, 1,024 units 1.4 us, 4,096
-// units 4 us, 8,000 to 32,768 units 5 to 7 us more than a table in device
-// memory).  At 8,192 units the two are even where the GPU is the limit.
-constexpr size_t DIRECT_UNITS_BYTES = 8192 * sizeof(Unit);
+// copy, an event and a wait (about 15 us a call, 30 us from 256 KiB on);
+// reading in place costs the kernel the link's latency and bandwidth (one unit
+// 0.5 us, 1,024 units 1.4 us, 4,096 units 4 us, 8,000 to 32,768 units 5 to 7 us
+// more than a table in device memory).  At 16,384 tiles of 4 KiB the kernel
+// takes 47 us, below what the host spends on such a call with the upload; at
+// 32,768 the kernel is the longer part.
+constexpr size_t DIRECT_UNITS_BYTES = 16384 * sizeof(Unit);
 
 // Takes the context's next staging slot for a call whose unit table has
 // ubytes bytes (need = device bytes with the in-place snapshots): waits for
@@ -601,12 +716,12 @@ int launch_planned(const LaunchCtx *ctx, const PlanView &v, const aes_schedule_t
         return AES_OK;
     }
     if ((e = launch_cbcdec_tiles(u_dec, (uint32_t)n_dec, v.max_bytes, d_scheds, n_scheds, ctx->d_timg,
-                                 d_preds, d_in, d_out, v.d_ctrs, ctx->tile_dec,
+                                 d_preds, d_in, d_out, v.d_ctrs, v.zero_ctrs, ctx->tile_dec,
                                  ctx->n_cu, stream)))
         return hip_fail((hipError_t)e);
     if ((e = launch_ctr_tiles(u_ctr, (uint32_t)n_ctr_tab, v.max_bytes, d_scheds, n_scheds, ctx->d_timg, d_in,
-                              d_out, v.d_ctrs + TILE_CTRS, ctx->tile_ctr, ctx->n_cu,
-                              stream)))
+                              d_out, v.d_ctrs + TILE_CTRS, v.zero_ctrs, ctx->tile_ctr,
+                              ctx->n_cu, stream)))
         return hip_fail((hipError_t)e);
     if ((e = launch_cbcenc_chains(u_chain, (uint32_t)v.n_chain, d_scheds, n_scheds, ctx->d_timg,
                                   d_in, d_out, ctx->chain, ctx->n_cu, stream)))
@@ -614,15 +729,14 @@ int launch_planned(const LaunchCtx *ctx, const PlanView &v, const aes_schedule_t
     return AES_OK;
 }
 
-// A few tiles of one side (n_dec or n_enc of them at `units`): launched with
-// the unit table among the kernel's arguments, so that the call takes no
-// staging buffer, copy or event.  False: not such a batch, nothing was launched.
-bool launch_few(aes_ctx *ctx, const Unit *units, size_t n_dec, size_t n_enc, size_t n_chain,
-                bool pred_in, uint32_t max_bytes, const aes_schedule_t *d_scheds,
+// A few tiles of one side, at `units` in host memory: launched with the unit
+// table among the kernel's arguments, so that the call takes no staging buffer,
+// copy or event.  False: not such a batch, nothing was launched.
+bool launch_few(aes_ctx *ctx, const Unit *units, const PlanView &v, const aes_schedule_t *d_scheds,
                 uint32_t n_scheds, const uint8_t *d_in, uint8_t *d_out, void *stream, int *st) {
-    const bool dec = n_dec > 0;
-    if (n_chain || (dec && n_enc) || n_dec + n_enc > INLINE_UNITS || (pred_in && d_in == d_out) ||
-        !is_default(dec ? ctx->tile_dec : ctx->tile_ctr) ||
+    const bool dec = v.n_dec > 0;
+    if (v.n_chain || (dec && v.n_ctr) || v.n_dec + v.n_ctr > INLINE_UNITS ||
+        (v.pred_in && d_in == d_out) || !is_default(dec ? ctx->tile_dec : ctx->tile_ctr) ||
         (dec ? ctx->dec_variant != AES_DEC_TABLE : ctx->ctr_variant != AES_CTR_TABLE))
         return false;
     const hipError_t e = hipSetDevice(ctx->device);
@@ -631,8 +745,8 @@ bool launch_few(aes_ctx *ctx, const Unit *units, size_t n_dec, size_t n_enc, siz
         return true;
     }
     int err = hipSuccess;
-    if (!launch_tiles_inline(dec, units, (uint32_t)(n_dec + n_enc), max_bytes, d_scheds, n_scheds,
-                             ctx->d_timg, d_in, d_out, ctx->n_cu, stream, &err))
+    if (!launch_tiles_inline(dec, units, (uint32_t)(v.n_dec + v.n_ctr), v.max_bytes, d_scheds,
+                             n_scheds, ctx->d_timg, d_in, d_out, ctx->n_cu, stream, &err))
         return false;
     *st = err == hipSuccess ? AES_OK : hip_fail((hipError_t)err);
     return true;
@@ -650,6 +764,37 @@ void pack_units(const Planned &p, void *dst) {
         memcpy(u, p.chains.data(), p.chains.size() * sizeof(Unit));
 }
 
+// Launches a slot's unit table on `stream` (uploading it if need be) and marks
+// the slot in use until that is done.
+int launch_slot(aes_ctx *ctx, Slot &s, PlanView v, const aes_schedule_t *d_scheds,
+                uint32_t n_scheds, const uint8_t *d_in, uint8_t *d_out, void *stream) {
+    const size_t n = v.n_dec + v.n_ctr + v.n_chain;
+    int st = upload_units(ctx, s, n * sizeof(Unit), stream, &v.d_units);
+    if (st)
+        return st;
+    v.d_preds = (Unit *)s.d_units + n;
+    v.d_ctrs = s.d_ctrs;
+    if ((st = launch_planned(ctx, v, d_scheds, n_scheds, d_in, d_out, stream)))
+        return st;
+    HIP_TRY(hipEventRecord(s.ev, (hipStream_t)stream));
+    s.ev_pending = true;
+    return AES_OK;
+}
+
+// A scanned batch as a PlanView without its memory.
+PlanView view_of(const BatchScan &b, uint32_t tile) {
+    PlanView v{};
+    v.n_dec = b.n_dec();
+    v.n_ctr = b.n_enc();
+    v.n_chain = b.n_chain();
+    v.pred_in = b.pred_in;
+    v.dec_bytes = b.dec_bytes();
+    v.ctr_bytes = b.enc_bytes();
+    v.max_bytes = (uint32_t)std::min<uint64_t>(tile, b.longest);
+    v.n_ecb = b.units[AES_OP_ECB_ENC];
+    return v;
+}
+
 int run_batch(aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_scheds,
               const uint8_t *d_in, uint8_t *d_out, uint64_t buf_bytes, const aes_req_t *reqs,
               uint64_t n, void *stream) {
@@ -658,37 +803,54 @@ int run_batch(aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_scheds,
     int st = check_buffers(d_in, d_out, buf_bytes, n, d_scheds);
     if (st)
         return st;
-    if ((st = validate(reqs, n, n_scheds, buf_bytes)))
+    if (n && !reqs)
+        return AES_ERR_ARG;
+    const uint32_t tile = ctx->tile_bytes;
+    BatchScan b;
+    if ((st = scan_requests(reqs, n, n_scheds, buf_bytes, tile, b)))
         return st;
-    Planned &p = ctx->scratch_plan;
-    if ((st = plan_units(reqs, n, ctx->tile_bytes, ctx->ctr_variant == AES_CTR_BITSLICE,
-                         ctx->dec_variant == AES_DEC_BITSLICE, p)))
-        return st;
-    if (!p.payload)
+    if (!b.sorted) {
+        std::vector<std::pair<uint64_t, uint64_t>> ranges;
+        try {
+            ranges.resize(n);
+        } catch (const std::bad_alloc &) {
+            return AES_ERR_NOMEM;
+        }
+        if ((st = check_disjoint(reqs, n, ranges.data())))
+            return st;
+    } else if (b.overlap) {
+        return AES_ERR_OVERLAP;
+    }
+    PlanView v = view_of(b, tile);
+    if (v.n_dec >= (1ull << 32) || v.n_ctr >= (1ull << 32) || v.n_chain >= (1ull << 32))
+        return AES_ERR_RANGE;
+    const uint64_t n_units = b.n_units();
+    if (!n_units)
         return AES_OK;
+    // The bitsliced kernels want their tiles grouped by key.
+    const bool group_ctr = ctx->ctr_variant == AES_CTR_BITSLICE && v.n_ctr;
+    const bool group_dec = ctx->dec_variant == AES_DEC_BITSLICE && v.n_dec;
+    Planned &p = ctx->scratch_plan;
+    if ((group_ctr || group_dec) &&
+        (st = plan_units(reqs, n, tile, group_ctr, group_dec, p)))
+        return st;
     if (ctx->device == AES_DEVICE_NONE)
         return AES_ERR_DEVICE;
-    if (launch_few(ctx, p.dec.empty() ? p.ctr.data() : p.dec.data(), p.dec.size(), p.ctr.size(),
-                   p.chains.size(), p.dec_has_pred_in, p.max_tile, d_scheds, n_scheds, d_in, d_out,
-                   stream, &st))
+    if (n_units <= INLINE_UNITS) {
+        Unit few[INLINE_UNITS];
+        write_units(reqs, n, tile, b, few);
+        if (launch_few(ctx, few, v, d_scheds, n_scheds, d_in, d_out, stream, &st))
+            return st;
+    }
+    Slot *s = nullptr;
+    if ((st = take_slot(ctx, n_units * sizeof(Unit), units_bytes(v.n_dec, v.n_ctr, v.n_chain),
+                        &s)))
         return st;
-    const size_t ubytes = (p.dec.size() + p.ctr.size() + p.chains.size()) * sizeof(Unit);
-    const size_t need = units_bytes(p.dec.size(), p.ctr.size(), p.chains.size());
-    Slot *sp = nullptr;
-    if ((st = take_slot(ctx, ubytes, need, &sp)))
-        return st;
-    Slot &s = *sp;
-    pack_units(p, s.h_stage);
-    const void *units = nullptr;
-    if ((st = upload_units(ctx, s, ubytes, stream, &units)))
-        return st;
-    st = launch_planned(ctx, view_of(p, units, s.d_units, s.d_ctrs), d_scheds, n_scheds, d_in,
-                        d_out, stream);
-    if (st)
-        return st;
-    HIP_TRY(hipEventRecord(s.ev, (hipStream_t)stream));
-    s.ev_pending = true;
-    return AES_OK;
+    if (group_ctr || group_dec)
+        pack_units(p, s->h_stage);
+    else
+        write_units(reqs, n, tile, b, (Unit *)s->h_stage);
+    return launch_slot(ctx, *s, v, d_scheds, n_scheds, d_in, d_out, stream);
 }
 
 // ------------------------------------------------- batches without allocation
@@ -745,64 +907,24 @@ int run_batch_noalloc(aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_s
         return st;
     if (n && !reqs)
         return AES_ERR_ARG;
-    // 1. The per-request rules (as validate), order, and the unit counts.
+    // 1. The per-request rules, order, and the unit counts.
     const uint32_t tile = ctx->tile_bytes;
-    uint64_t n_dec = 0, n_ctr = 0, n_ecb = 0, n_chain = 0, n_live = 0, payload = 0;
-    uint64_t dec_bytes = 0, ctr_bytes = 0, last_off = 0;
-    bool sorted = true, pred_in = false;
-    for (uint64_t i = 0; i < n; i++) {
-        const aes_req_t &r = reqs[i];
-        if (r.op > AES_OP_ECB_DEC)
-            return AES_ERR_ARG;
-        if ((st = check_request(r.op, r.offset, r.length, r.key_idx, n_scheds, buf_bytes)))
-            return st;
-        if (!r.length)
-            continue;
-        if (r.offset < last_off)
-            sorted = false;
-        last_off = r.offset;
-        n_live++;
-        payload += r.length;
-        const uint64_t t = (r.length + tile - 1) / tile;
-        if (r.op == AES_OP_CBC_ENC) {
-            n_chain++;
-        } else if (is_dec_tile_op(r.op)) {
-            n_dec += t;
-            dec_bytes += r.length;
-            pred_in |= r.op == AES_OP_CBC_DEC && t > 1;
-        } else {
-            (r.op == AES_OP_CTR ? n_ctr : n_ecb) += t;
-            ctr_bytes += r.length;
-        }
-    }
-    const uint64_t n_units = n_dec + n_ctr + n_ecb + n_chain;
+    BatchScan b;
+    if ((st = scan_requests(reqs, n, n_scheds, buf_bytes, tile, b)))
+        return st;
+    const uint64_t n_units = b.n_units();
     if (n_units > AES_NOALLOC_MAX_UNITS)
         return AES_ERR_RANGE;
     std::lock_guard<std::mutex> lk(g_noalloc_mu);
-    // 2. Disjoint output ranges: a linear scan in offset order, else a sort
-    //    of (offset, end) pairs in the static array (n_live <= n_units).
-    if (sorted) {
-        uint64_t end = 0;
-        bool any = false;
-        for (uint64_t i = 0; i < n; i++) {
-            if (!reqs[i].length)
-                continue;
-            if (any && reqs[i].offset < end)
-                return AES_ERR_OVERLAP;
-            end = reqs[i].offset + reqs[i].length;
-            any = true;
-        }
-    } else {
-        uint64_t k = 0;
-        for (uint64_t i = 0; i < n; i++)
-            if (reqs[i].length)
-                g_noalloc_ranges[k++] = {reqs[i].offset, reqs[i].offset + reqs[i].length};
-        std::sort(g_noalloc_ranges, g_noalloc_ranges + k);
-        for (uint64_t i = 1; i < k; i++)
-            if (g_noalloc_ranges[i].first < g_noalloc_ranges[i - 1].second)
-                return AES_ERR_OVERLAP;
+    // 2. Disjoint output ranges (as many as there are nonempty requests, at
+    //    most n_units, where they have to be sorted).
+    if (!b.sorted) {
+        if ((st = check_disjoint(reqs, n, g_noalloc_ranges)))
+            return st;
+    } else if (b.overlap) {
+        return AES_ERR_OVERLAP;
     }
-    if (!payload)
+    if (!n_units)
         return AES_OK;
     if (ctx->device == AES_DEVICE_NONE)
         return AES_ERR_DEVICE;
@@ -810,74 +932,31 @@ int run_batch_noalloc(aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_s
         ctx->device < NOALLOC_MAX_DEVICES ? g_scratch_ptr[ctx->device] : nullptr;
     if (!d_scratch)
         return AES_ERR_DEVICE;
-    // 3. Unit records, as plan_units cuts them: [CBC/ECB-decrypt tiles | CTR
-    //    tiles | ECB-encrypt tiles | chains], tiles in request order, chains
-    //    longest first (equal lengths by key index, then offset).
-    Unit *w_dec = g_noalloc_units, *w_ctr = w_dec + n_dec, *w_ecb = w_ctr + n_ctr;
-    Unit *w_chain = w_ecb + n_ecb;
-    for (uint64_t i = 0; i < n; i++) {
-        const aes_req_t &r = reqs[i];
-        if (!r.length)
-            continue;
-        const uint32_t meta = r.key_idx | (r.op << META_OP_SHIFT);
-        if (r.op == AES_OP_CBC_ENC) {
-            Unit &u = *w_chain++;
-            u.off = r.offset;
-            u.nbytes = (uint32_t)r.length;
-            u.meta = meta;
-            for (int j = 0; j < 4; j++)
-                u.w[j] = le32(r.iv + 4 * j);
-            continue;
-        }
-        const uint64_t ctr0 = be64(r.iv + 8);
-        for (uint64_t pos = 0; pos < r.length; pos += tile) {
-            Unit &u = r.op == AES_OP_CTR ? *w_ctr++ : r.op == AES_OP_ECB_ENC ? *w_ecb++ : *w_dec++;
-            u.off = r.offset + pos;
-            u.nbytes = (uint32_t)std::min<uint64_t>(tile, r.length - pos);
-            u.meta = meta;
-            if (r.op == AES_OP_CTR) {
-                const uint64_t c = ctr0 + pos / 16;  // mod 2^64, nonce untouched
-                u.w[0] = le32(r.iv);
-                u.w[1] = le32(r.iv + 4);
-                u.w[2] = (uint32_t)c;
-                u.w[3] = (uint32_t)(c >> 32);
-            } else if (r.op == AES_OP_CBC_DEC && pos == 0) {
-                for (int j = 0; j < 4; j++)
-                    u.w[j] = le32(r.iv + 4 * j);
-            } else {
-                if (r.op == AES_OP_CBC_DEC)
-                    u.meta |= FLAG_PRED_IN;
-                u.w[0] = u.w[1] = u.w[2] = u.w[3] = 0;
-            }
-        }
-    }
-    Unit *chains = g_noalloc_units + n_dec + n_ctr + n_ecb;
-    std::sort(chains, chains + n_chain, [](const Unit &a, const Unit &b) {
-        const uint32_t ka = a.meta & META_KEY_MASK, kb = b.meta & META_KEY_MASK;
-        if (a.nbytes != b.nbytes)
-            return a.nbytes > b.nbytes;
-        return ka != kb ? ka < kb : a.off < b.off;
-    });
+    // 3. Unit records; few of them travel with the launch.
+    write_units(reqs, n, tile, b, g_noalloc_units);
+    PlanView v = view_of(b, tile);
+    if (launch_few(ctx, g_noalloc_units, v, d_scheds, n_scheds, d_in, d_out, stream, &st))
+        return st;
     // 4. Upload (the static host array is read before the copy call returns,
-    //    as for any copy from pageable memory), zero the tile counters, launch.
+    //    as for any copy from pageable memory) and launch; a kernel that uses
+    //    the tile counters has them cleared first.
     HIP_TRY(hipSetDevice(ctx->device));
     HIP_TRY(hipMemcpyAsync(d_scratch, g_noalloc_units, n_units * sizeof(Unit),
                            hipMemcpyHostToDevice, (hipStream_t)stream));
-    uint32_t *d_ctrs = (uint32_t *)((uint8_t *)d_scratch + NOALLOC_CTRS_OFF);
-    int e = launch_zero_words(d_ctrs, 2 * TILE_CTRS, stream);
-    if (e)
-        return hip_fail((hipError_t)e);
-    const PlanView v{d_scratch, (Unit *)d_scratch + n_units, d_ctrs, (size_t)n_dec, (size_t)(n_ctr + n_ecb), (size_t)n_chain,
-                     pred_in, dec_bytes, ctr_bytes, tile, (size_t)n_ecb};
+    v.d_units = d_scratch;
+    v.d_preds = (Unit *)d_scratch + n_units;
+    v.d_ctrs = (uint32_t *)((uint8_t *)d_scratch + NOALLOC_CTRS_OFF);
+    v.zero_ctrs = true;
     return launch_planned(ctx, v, d_scheds, n_scheds, d_in, d_out, stream);
 }
 
-// --------------------------------------------- large single-op calls, in parallel
+// ------------------------------------------------- single-op calls over tiles
 
-// Requests per chunk of the parallel single-call path, and the smallest call
-// it takes (below that, thread hand-off costs more than it saves).
+// Requests per chunk of a single-op call over tiles, and the smallest call
+// whose chunks are shared with the context's threads (below that, thread
+// hand-off costs more than it saves).
 constexpr uint64_t PAR_CHUNK = 4096;
-constexpr uint64_t PAR_MIN_REQS = 2 * PAR_CHUNK;
+constexpr uint64_t PAR_MIN_REQS = 4 * PAR_CHUNK;
 constexpr int PAR_MAX_THREADS = 8;
 
 struct ChunkScan {
@@ -885,28 +964,28 @@ struct ChunkScan {
     int err = AES_OK;
     bool ordered = true;  // nonzero requests in offset order and disjoint
     uint64_t first_off = UINT64_MAX, last_end = 0;
-    uint64_t tiles = 0, payload = 0, extent = 0, longest = 0;
+    uint64_t tiles = 0, payload = 0, longest = 0;
     bool pred_in = false;
 };
 
-// A single-op call over tiles (CBC decryption, CTR, ECB) with many requests:
-// the requests are checked in chunks on the context's threads (same rules and
-// error precedence as validate), then each chunk writes its unit records
+// A single-op call over tiles (CBC decryption, CTR, ECB): the requests are
+// checked in chunks (on the context's threads if there are many; the rules and
+// error precedence of validate), then each chunk writes its unit records
 // straight into the pinned staging buffer at offsets from a prefix sum, in
 // request order.  Returns 1 when the call is not for this path.
-int single_parallel(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds,
-                    uint32_t n_scheds, const uint8_t *d_in, uint8_t *d_out, uint64_t buf_bytes,
-                    const uint64_t *offsets, const uint64_t *lengths, const uint32_t *key_idx,
-                    const uint8_t *ivs, uint64_t n, void *stream) {
-    if (n < PAR_MIN_REQS || op == AES_OP_CBC_ENC ||
-        (op == AES_OP_CTR && ctx->ctr_variant == AES_CTR_BITSLICE) ||
+int single_tiles(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_scheds,
+                 const uint8_t *d_in, uint8_t *d_out, uint64_t buf_bytes,
+                 const uint64_t *offsets, const uint64_t *lengths, const uint32_t *key_idx,
+                 const uint8_t *ivs, uint64_t n, void *stream) {
+    if (op == AES_OP_CBC_ENC || (op == AES_OP_CTR && ctx->ctr_variant == AES_CTR_BITSLICE) ||
         (is_dec_tile_op(op) && ctx->dec_variant == AES_DEC_BITSLICE) ||
         n / PAR_CHUNK >= (1ull << 30))
         return 1;
     int st = check_buffers(d_in, d_out, buf_bytes, n, d_scheds);
     if (st)
         return st;
-    if (!ctx->pool) {
+    const bool threads = n >= PAR_MIN_REQS;
+    if (threads && !ctx->pool) {
         const unsigned hw = std::thread::hardware_concurrency();
         const int t = (int)std::min<unsigned>(hw ? hw : 1, PAR_MAX_THREADS);
         try {
@@ -918,6 +997,14 @@ int single_parallel(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds,
     const uint32_t tile = ctx->tile_bytes;
     const bool dec = is_dec_tile_op(op);
     const uint64_t n_chunks = (n + PAR_CHUNK - 1) / PAR_CHUNK;
+    const auto run = [&](const auto &chunk) {
+        if (threads) {
+            ctx->pool->run((int)n_chunks, chunk);
+        } else {
+            for (uint64_t c = 0; c < n_chunks; c++)
+                chunk((int)c);
+        }
+    };
     std::vector<ChunkScan> sc;
     std::vector<uint64_t> base;
     try {
@@ -927,8 +1014,8 @@ int single_parallel(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds,
         return AES_ERR_NOMEM;
     }
     // 1. Rules, order and unit counts per chunk.
-    ctx->pool->run((int)n_chunks, [&](int c) {
-        ChunkScan &k = sc[c];
+    run([&](int c) {
+        ChunkScan k;
         const uint64_t lo = (uint64_t)c * PAR_CHUNK, hi = std::min(n, lo + PAR_CHUNK);
         for (uint64_t i = lo; i < hi; i++) {
             const uint64_t off = offsets[i], len = lengths[i];
@@ -936,7 +1023,7 @@ int single_parallel(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds,
             if (e) {
                 k.err_at = i;
                 k.err = e;
-                return;
+                break;
             }
             if (!len)
                 continue;
@@ -945,12 +1032,12 @@ int single_parallel(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds,
             if (k.first_off == UINT64_MAX)
                 k.first_off = off;
             k.last_end = std::max(k.last_end, off + len);
-            k.tiles += (len + tile - 1) / tile;
+            k.tiles += tile_count(len, tile);
             k.payload += len;
-            k.extent = std::max(k.extent, off + len);
             k.longest = std::max(k.longest, len);
-            k.pred_in |= dec && op == AES_OP_CBC_DEC && len > tile;
         }
+        k.pred_in = op == AES_OP_CBC_DEC && k.longest > tile;
+        sc[c] = k;
     });
     // 2. The first error in request order, then disjointness.
     uint64_t err_at = UINT64_MAX, payload = 0, longest = 0;
@@ -995,58 +1082,36 @@ int single_parallel(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds,
         return AES_OK;
     if (ctx->device == AES_DEVICE_NONE)
         return AES_ERR_DEVICE;
-    const size_t n_dec = dec ? n_tiles : 0, n_enc = dec ? 0 : n_tiles;
-    const size_t ubytes = n_tiles * sizeof(Unit);
-    const size_t need = units_bytes(n_dec, n_enc, 0);
-    Slot *sp = nullptr;
-    if ((st = take_slot(ctx, ubytes, need, &sp)))
+    PlanView v{};
+    v.n_dec = dec ? n_tiles : 0;
+    v.n_ctr = dec ? 0 : n_tiles;
+    v.pred_in = pred_in;
+    v.dec_bytes = dec ? payload : 0;
+    v.ctr_bytes = dec ? 0 : payload;
+    v.max_bytes = (uint32_t)std::min<uint64_t>(tile, longest);
+    v.n_ecb = op == AES_OP_ECB_ENC ? n_tiles : 0;
+    // 3. Unit records, in request order.
+    const auto write = [&](uint64_t lo, uint64_t hi, Unit *u) {
+        for (uint64_t i = lo; i < hi; i++)
+            if (lengths[i])
+                u = write_request(op, offsets[i], lengths[i], key_idx[i],
+                                  ivs ? ivs + 16 * i : nullptr, tile, u);
+    };
+    if (n_tiles <= INLINE_UNITS) {
+        Unit few[INLINE_UNITS];
+        write(0, n, few);
+        if (launch_few(ctx, few, v, d_scheds, n_scheds, d_in, d_out, stream, &st))
+            return st;
+    }
+    Slot *s = nullptr;
+    if ((st = take_slot(ctx, n_tiles * sizeof(Unit), units_bytes(v.n_dec, v.n_ctr, 0), &s)))
         return st;
-    Slot &s = *sp;
-    // 3. Unit records, in request order, into the staging buffer.
-    Unit *out = (Unit *)s.h_stage;
-    ctx->pool->run((int)n_chunks, [&](int c) {
-        const uint64_t lo = (uint64_t)c * PAR_CHUNK, hi = std::min(n, lo + PAR_CHUNK);
-        Unit *u = out + base[c];
-        for (uint64_t i = lo; i < hi; i++) {
-            const uint64_t off = offsets[i], len = lengths[i];
-            if (!len)
-                continue;
-            const uint32_t meta = key_idx[i] | (op << META_OP_SHIFT);
-            const uint8_t *iv = ivs ? ivs + 16 * i : nullptr;
-            const uint64_t ctr0 = op == AES_OP_CTR ? be64(iv + 8) : 0;
-            for (uint64_t pos = 0; pos < len; pos += tile, u++) {
-                u->off = off + pos;
-                u->nbytes = (uint32_t)std::min<uint64_t>(tile, len - pos);
-                u->meta = meta;
-                if (op == AES_OP_CTR) {
-                    const uint64_t ctr = ctr0 + pos / 16;  // mod 2^64, nonce untouched
-                    u->w[0] = le32(iv);
-                    u->w[1] = le32(iv + 4);
-                    u->w[2] = (uint32_t)ctr;
-                    u->w[3] = (uint32_t)(ctr >> 32);
-                } else if (op == AES_OP_CBC_DEC && pos == 0) {
-                    for (int w = 0; w < 4; w++)
-                        u->w[w] = le32(iv + 4 * w);
-                } else {
-                    if (op == AES_OP_CBC_DEC)
-                        u->meta |= FLAG_PRED_IN;
-                    u->w[0] = u->w[1] = u->w[2] = u->w[3] = 0;
-                }
-            }
-        }
+    Unit *out = (Unit *)s->h_stage;
+    run([&](int c) {
+        const uint64_t lo = (uint64_t)c * PAR_CHUNK;
+        write(lo, std::min(n, lo + PAR_CHUNK), out + base[c]);
     });
-    const void *units = nullptr;
-    if ((st = upload_units(ctx, s, ubytes, stream, &units)))
-        return st;
-    PlanView v{units, (Unit *)s.d_units + n_tiles, s.d_ctrs, n_dec, n_enc, 0, pred_in,
-               dec ? payload : 0, dec ? 0 : payload,
-               (uint32_t)std::min<uint64_t>(tile, longest), op == AES_OP_ECB_ENC ? n_enc : 0};
-    st = launch_planned(ctx, v, d_scheds, n_scheds, d_in, d_out, stream);
-    if (st)
-        return st;
-    HIP_TRY(hipEventRecord(s.ev, (hipStream_t)stream));
-    s.ev_pending = true;
-    return AES_OK;
+    return launch_slot(ctx, *s, v, d_scheds, n_scheds, d_in, d_out, stream);
 }
 
 int single_mode(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_scheds,
@@ -1058,8 +1123,8 @@ int single_mode(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds, uint3
     const bool ecb = op == AES_OP_ECB_ENC || op == AES_OP_ECB_DEC;  // no IVs
     if (n && (!offsets || !lengths || !key_idx || (!ivs && !ecb)))
         return AES_ERR_ARG;
-    const int pst = single_parallel(op, ctx, d_scheds, n_scheds, d_in, d_out, buf_bytes, offsets,
-                                    lengths, key_idx, ecb ? nullptr : ivs, n, stream);
+    const int pst = single_tiles(op, ctx, d_scheds, n_scheds, d_in, d_out, buf_bytes, offsets,
+                                 lengths, key_idx, ecb ? nullptr : ivs, n, stream);
     if (pst != 1)
         return pst;
     std::vector<aes_req_t> &reqs = ctx->scratch_reqs;

@@ -104,12 +104,13 @@ inline TileKernel pick_tile_kernel(int nb, int wg) {
     return nullptr;
 }
 
-// d_ctrs: TILE_MAX_GRID zeroed counters (zero again after every launch).
+// d_ctrs: TILE_MAX_GRID zeroed counters (zero again after every launch), or,
+// with zero_ctrs, any.
 template <bool DEC>
 inline int launch_tiles(const Unit *d_units, uint32_t n_units, uint32_t max_bytes,
                         const aes_schedule_t *d_sched, uint32_t n_sched, const uint32_t *d_timg,
                         const void *d_preds, const uint8_t *d_in, uint8_t *d_out,
-                        uint32_t *d_ctrs, const TileLaunch &cfg, int n_cu,
+                        uint32_t *d_ctrs, bool zero_ctrs, const TileLaunch &cfg, int n_cu,
                         void *stream) {
     if (!n_units)
         return hipSuccess;
@@ -132,6 +133,12 @@ inline int launch_tiles(const Unit *d_units, uint32_t n_units, uint32_t max_byte
         grid = 1;
     if (!d_ctrs || (uint32_t)grid > TILE_MAX_GRID)
         return hipErrorInvalidValue;
+    if (zero_ctrs) {
+        const uint32_t words = (uint32_t)grid * ((uint32_t)grid <= TILE_SPREAD_GRID
+                                                     ? TILE_CTR_STRIDE : 1u);
+        if ((err = launch_zero_words(d_ctrs, words, stream)))
+            return err;
+    }
     hipLaunchKernelGGL(k, dim3(grid), dim3(cfg.wg_threads), 0, (hipStream_t)stream, d_units,
                        n_units / grid, n_units % grid, d_sched, n_sched, d_timg,
                        (const uint4 *)d_preds, d_in, d_out, d_ctrs);
