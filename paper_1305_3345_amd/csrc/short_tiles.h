@@ -35,6 +35,46 @@ __device__ __forceinline__ void buffer_block(const uint8_t *base, uint32_t nbyte
     x[3] = v.w;
 }
 
+// The first n bytes (1..15) of a block, the rest zero: at most one load each
+// of 8, 4, 2 and 1 bytes, all in flight together and none past the end (a loop
+// over the bytes waited for each: 65,536 CTR units of 1 to 1,024 B took 92.7 us
+// with it, 63.7 without).
+__device__ __forceinline__ void load_tail(const uint8_t *p, uint32_t n, uint32_t x[4]) {
+    uint2 a = make_uint2(0u, 0u);
+    uint32_t b = 0u, c = 0u, d = 0u;
+    if (n & 8u)
+        a = *reinterpret_cast<const uint2 *>(p);
+    if (n & 4u)
+        b = *reinterpret_cast<const uint32_t *>(p + (n & 8u));
+    if (n & 2u)
+        c = *reinterpret_cast<const uint16_t *>(p + (n & 12u));
+    if (n & 1u)
+        d = p[n & 14u];
+    const uint32_t t = c | d << ((n & 2u) << 3);  // the last one to three bytes
+    const uint32_t lo = n & 4u ? b : t, hi = n & 4u ? t : 0u;
+    x[0] = n & 8u ? a.x : lo;
+    x[1] = n & 8u ? a.y : hi;
+    x[2] = n & 8u ? lo : 0u;
+    x[3] = n & 8u ? hi : 0u;
+}
+
+// Stores the first n bytes (1..15) of a block, in the same pieces.  (Chosen
+// with masks: a choice between elements of o would be made between their
+// addresses and put o into scratch memory.)
+__device__ __forceinline__ void store_tail(uint8_t *p, uint32_t n, const uint32_t o[4]) {
+    const uint32_t m8 = 0u - ((n >> 3) & 1u), m4 = 0u - ((n >> 2) & 1u);
+    if (n & 8u)
+        *reinterpret_cast<uint2 *>(p) = make_uint2(o[0], o[1]);
+    const uint32_t lo = (o[2] & m8) | (o[0] & ~m8), hi = (o[3] & m8) | (o[1] & ~m8);
+    if (n & 4u)
+        *reinterpret_cast<uint32_t *>(p + (n & 8u)) = lo;
+    const uint32_t t = (hi & m4) | (lo & ~m4);
+    if (n & 2u)
+        *reinterpret_cast<uint16_t *>(p + (n & 12u)) = (uint16_t)t;
+    if (n & 1u)
+        p[n & 14u] = (uint8_t)(t >> ((n & 2u) << 3));
+}
+
 // One wave's part of a unit, bytes [part * NB KiB, ...) of it (at most NB KiB).
 template <bool DEC, int NB>
 struct Part {
@@ -160,15 +200,18 @@ struct Part {
                                           uint8_t *out) const {
 #pragma unroll
         for (int i = 0; i < NB; i++) {
-            const uint32_t b = 64u * i + lane;
-            if (!DEC && (nbytes & 15u) && b == nbytes >> 4) {  // a partial block (CTR)
+            const uint32_t start = (64u * i + lane) * 16u;
+            if (start + 16u <= nbytes) {
+                *reinterpret_cast<uint4 *>(out + at + start) =
+                    make_uint4(o[i][0], o[i][1], o[i][2], o[i][3]);
+            } else if (!DEC && start < nbytes) {  // a partial block (CTR)
                 uint32_t m[4];
-                load_block(in + at, b, nbytes, m);
+                load_tail(in + at + start, nbytes - start, m);
 #pragma unroll
                 for (int j = 0; j < 4; j++)
-                    o[i][j] ^= m[j];
+                    m[j] ^= o[i][j];
+                store_tail(out + at + start, nbytes - start, m);
             }
-            store_block(out + at, b, nbytes, o[i]);
         }
     }
 };

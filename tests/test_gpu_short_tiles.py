@@ -94,6 +94,24 @@ def test_unit_counts(fresh, op, n, inplace):
 
 @pytest.mark.parametrize("inplace", [False, True])
 @pytest.mark.parametrize("op", list(OPS))
+@pytest.mark.parametrize("n", [4096, 4097, 20011])
+def test_many_small_units(ctx, op, n, inplace):
+    """Units of at most 1 KiB in any number: one pass of sixteen waves on 256
+    compute units, its first unit more, and about five passes; every tail
+    length of CTR."""
+    print(f"[gpu] small units: {op}, {n} units, inplace={inplace}", flush=True)
+    lengths = np.random.default_rng(n).integers(1, 1025, n)
+    if op != "ctr":
+        lengths = (lengths + 15) // 16 * 16
+    wl = requests(op, lengths, n)
+    inp = wl.data()
+    msg = first_mismatch(run_gpu(ctx, wl, inp, form="plan", inplace=inplace),
+                         run_oracle(wl, inp, inplace=inplace))
+    assert msg is None, msg
+
+
+@pytest.mark.parametrize("inplace", [False, True])
+@pytest.mark.parametrize("op", list(OPS))
 def test_requests_by_value(ctx, op, inplace):
     """One request per launch: one block to 12 MiB and a block (the first size
     beyond these kernels where the parts spread over the device)."""
