@@ -1,5 +1,5 @@
 """GPU parity of batches around the size at which the unit table stops being
-read from the pinned staging buffer and is uploaded instead (8,192 units), with
+read from the pinned staging buffer and is uploaded instead (16,384 units), with
 more calls in flight than the context has staging slots, on one stream and on
 two in turn: each call has its own requests (keys, IVs, order of lengths) and
 output, so a table read after its slot was taken again shows."""
@@ -28,7 +28,7 @@ def mixed_requests(n_units, seed):
     return workloads.Workload("unit_tables", reqs, keys, kb, 64 * n_units, seed)
 
 
-@pytest.mark.parametrize("n_units", [1, 8192, 8193])
+@pytest.mark.parametrize("n_units", [1, 16384, 16385])
 @pytest.mark.parametrize("streams", [1, 2])
 def test_tables_in_flight(n_units, streams):
     print(f"[gpu] {n_units} units, six calls in flight on {streams} stream(s)", flush=True)
