@@ -122,7 +122,7 @@ bool is_enc_tile_op(uint32_t op) { return op == AES_OP_CTR || op == AES_OP_ECB_E
 // and bytes by operation, and whether the nonempty requests come in offset
 // order without overlapping.
 struct BatchScan {
-    uint64_t units[5] = {0, 0, 0, 0, 0}, bytes[5] = {0, 0, 0, 0, 0};
+    uint64_t units[5] = {0, 0, 0, 0, 0}, bytes[5] = {0, 0, 0, 0, 0}, kib[5] = {0, 0, 0, 0, 0};
     uint64_t longest = 0;  // bytes of the longest request with tiles
     bool sorted = true, overlap = false, pred_in = false;
     uint64_t n_dec() const { return units[AES_OP_CBC_DEC] + units[AES_OP_ECB_DEC]; }
@@ -132,6 +132,9 @@ struct BatchScan {
     uint64_t dec_bytes() const { return bytes[AES_OP_CBC_DEC] + bytes[AES_OP_ECB_DEC]; }
     uint64_t enc_bytes() const { return bytes[AES_OP_CTR] + bytes[AES_OP_ECB_ENC]; }
 };
+
+// Parts of 1 KiB of a request's tiles (tiles are multiples of 1 KiB).
+inline uint64_t kib_parts(uint64_t len) { return (len + 1023) >> 10; }
 
 inline uint64_t tile_count(uint64_t len, uint32_t tile) {
     return len <= tile ? 1 : (len + tile - 1) / tile;  // most requests: no division
@@ -156,6 +159,7 @@ int scan_requests(const aes_req_t *reqs, uint64_t n, uint32_t n_scheds, uint64_t
         last_off = r.offset;
         end = r.offset + r.length;
         b.bytes[r.op] += r.length;
+        b.kib[r.op] += kib_parts(r.length);
         if (r.op == AES_OP_CBC_ENC) {
             b.units[r.op]++;
             continue;
@@ -222,6 +226,7 @@ struct Planned {
     uint64_t extent = 0;
     uint64_t dec_bytes = 0, ctr_bytes = 0, chain_bytes = 0;
     uint32_t max_tile = 0;  // bytes of the largest tile
+    uint64_t enc_kib = 0;   // parts of 1 KiB of the encryption tiles
     bool dec_has_pred_in = false;
     size_t n_ecb = 0;  // ECB-encrypt tiles at the end of ctr
     std::vector<Unit> ecb;       // ECB-encrypt tiles while planning (appended to ctr)
@@ -236,6 +241,7 @@ struct Planned {
         chains.clear();
         payload = extent = 0;
         max_tile = 0;
+        enc_kib = 0;
         dec_bytes = ctr_bytes = chain_bytes = 0;
         dec_has_pred_in = false;
         n_ecb = 0;
@@ -419,6 +425,8 @@ int plan_units(const aes_req_t *reqs, uint64_t n, uint32_t tile_bytes, bool grou
                 p.max_tile = (uint32_t)std::max<uint64_t>(
                     p.max_tile, std::min<uint64_t>(tile_bytes, r.length));
             p.dec_has_pred_in |= r.op == AES_OP_CBC_DEC && t > 1;
+            if (is_enc_tile_op(r.op))
+                p.enc_kib += kib_parts(r.length);
             const size_t at = v.size();
             v.resize(at + t);
             write_request(r.op, r.offset, r.length, r.key_idx, r.iv, tile_bytes, v.data() + at);
@@ -528,6 +536,7 @@ struct PlanView {
     bool pred_in;
     uint64_t dec_bytes, ctr_bytes;
     uint32_t max_bytes;  // no tile is larger
+    uint64_t enc_kib;  // parts of 1 KiB of the encryption tiles
     size_t n_ecb;  // ECB-encrypt tiles: the last n_ecb of the n_ctr encryption tiles
     bool zero_ctrs;  // the counters may not be zero: clear what a launch uses first
 };
@@ -537,7 +546,7 @@ struct PlanView {
 PlanView view_of(const Planned &p, const void *units, void *d_units, uint32_t *d_ctrs) {
     return PlanView{units, (Unit *)d_units + (p.dec.size() + p.ctr.size() + p.chains.size()),
                     d_ctrs, p.dec.size(), p.ctr.size(), p.chains.size(), p.dec_has_pred_in,
-                    p.dec_bytes, p.ctr_bytes, p.max_tile, p.n_ecb, false};
+                    p.dec_bytes, p.ctr_bytes, p.max_tile, p.enc_kib, p.n_ecb, false};
 }
 
 }  // namespace
@@ -612,7 +621,8 @@ int take_slot(aes_ctx *ctx, size_t ubytes, size_t need, Slot **out) {
             (void)hipHostFree(s.h_stage);
         s.h_stage = s.d_stage = nullptr;
         s.h_cap = 0;
-        if (hipHostMalloc(&s.h_stage, ubytes, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
+        if (hipHostMalloc(&s.h_stage, ubytes, hipHostMallocMapped | hipHostMallocCoherent) !=
+            hipSuccess)
             return AES_ERR_NOMEM;
         if (hipHostGetDevicePointer(&s.d_stage, s.h_stage, 0) != hipSuccess) {
             (void)hipHostFree(s.h_stage);
@@ -751,13 +761,13 @@ int launch_planned(const LaunchCtx *ctx, const PlanView &v, const aes_schedule_t
             return hip_fail((hipError_t)e);
         return AES_OK;
     }
-    if ((e = launch_cbcdec_tiles(u_dec, (uint32_t)n_dec, v.max_bytes, d_scheds, n_scheds, ctx->d_timg,
-                                 d_preds, d_in, d_out, v.d_ctrs, v.zero_ctrs, ctx->tile_dec,
-                                 ctx->n_cu, stream)))
+    if ((e = launch_cbcdec_tiles(u_dec, (uint32_t)n_dec, v.max_bytes, d_scheds, n_scheds,
+                                 ctx->d_timg, d_preds, d_in, d_out, v.d_ctrs, v.zero_ctrs,
+                                 ctx->tile_dec, ctx->n_cu, stream)))
         return hip_fail((hipError_t)e);
-    if ((e = launch_ctr_tiles(u_ctr, (uint32_t)n_ctr_tab, v.max_bytes, d_scheds, n_scheds, ctx->d_timg, d_in,
-                              d_out, v.d_ctrs + TILE_CTRS, v.zero_ctrs, ctx->tile_ctr,
-                              ctx->n_cu, stream)))
+    if ((e = launch_ctr_tiles(u_ctr, (uint32_t)n_ctr_tab, v.max_bytes, v.enc_kib, d_scheds,
+                              n_scheds, ctx->d_timg, d_in, d_out, v.d_ctrs + TILE_CTRS,
+                              v.zero_ctrs, ctx->tile_ctr, ctx->n_cu, stream)))
         return hip_fail((hipError_t)e);
     if ((e = launch_cbcenc_chains(u_chain, (uint32_t)v.n_chain, d_scheds, n_scheds, ctx->d_timg,
                                   d_in, d_out, ctx->chain, ctx->n_cu, stream)))
@@ -827,6 +837,7 @@ PlanView view_of(const BatchScan &b, uint32_t tile) {
     v.dec_bytes = b.dec_bytes();
     v.ctr_bytes = b.enc_bytes();
     v.max_bytes = (uint32_t)std::min<uint64_t>(tile, b.longest);
+    v.enc_kib = b.kib[AES_OP_CTR] + b.kib[AES_OP_ECB_ENC];
     v.n_ecb = b.units[AES_OP_ECB_ENC];
     return v;
 }
@@ -1008,7 +1019,7 @@ struct ChunkScan {
     int err = AES_OK;
     bool ordered = true;  // nonzero requests in offset order and disjoint
     uint64_t first_off = UINT64_MAX, last_end = 0;
-    uint64_t tiles = 0, payload = 0, longest = 0;
+    uint64_t tiles = 0, payload = 0, longest = 0, kib = 0;
     bool pred_in = false;
 };
 
@@ -1078,13 +1089,14 @@ int single_tiles(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds, uint
             k.last_end = std::max(k.last_end, off + len);
             k.tiles += tile_count(len, tile);
             k.payload += len;
+            k.kib += kib_parts(len);
             k.longest = std::max(k.longest, len);
         }
         k.pred_in = op == AES_OP_CBC_DEC && k.longest > tile;
         sc[c] = k;
     });
     // 2. The first error in request order, then disjointness.
-    uint64_t err_at = UINT64_MAX, payload = 0, longest = 0;
+    uint64_t err_at = UINT64_MAX, payload = 0, longest = 0, kib = 0;
     bool ordered = true, pred_in = false;
     uint64_t prev_end = 0;
     base[0] = 0;
@@ -1098,6 +1110,7 @@ int single_tiles(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds, uint
         if (sc[c].first_off != UINT64_MAX)
             prev_end = sc[c].last_end;
         payload += sc[c].payload;
+        kib += sc[c].kib;
         longest = std::max(longest, sc[c].longest);
         pred_in |= sc[c].pred_in;
         base[c + 1] = base[c] + sc[c].tiles;
@@ -1133,6 +1146,7 @@ int single_tiles(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds, uint
     v.dec_bytes = dec ? payload : 0;
     v.ctr_bytes = dec ? 0 : payload;
     v.max_bytes = (uint32_t)std::min<uint64_t>(tile, longest);
+    v.enc_kib = dec ? 0 : kib;
     v.n_ecb = op == AES_OP_ECB_ENC ? n_tiles : 0;
     // 3. Unit records, in request order.
     const auto write = [&](uint64_t lo, uint64_t hi, Unit *u) {
@@ -1437,8 +1451,8 @@ int aes_plan_launch(aes_plan_t *plan, const aes_schedule_t *d_scheds, const uint
     if (ctx->device == AES_DEVICE_NONE)
         return AES_ERR_DEVICE;
     HIP_TRY(hipSetDevice(ctx->device));
-    return launch_planned(ctx, view_of(plan->p, plan->d_units, plan->d_units, plan->d_ctrs), d_scheds, plan->n_scheds, d_in,
-                          d_out, stream);
+    return launch_planned(ctx, view_of(plan->p, plan->d_units, plan->d_units, plan->d_ctrs),
+                          d_scheds, plan->n_scheds, d_in, d_out, stream);
 }
 
 int aes_plan_info(const aes_plan_t *plan, aes_plan_info_t *info) {
@@ -1574,7 +1588,8 @@ int aes_request_launch(aes_ctx_t *ctx, const aes_schedule_t *d_scheds, uint32_t 
     if (ctx->device == AES_DEVICE_NONE)
         return AES_ERR_DEVICE;
     HIP_TRY(hipSetDevice(ctx->device));
-    const int e = launch_request(*req, request_tile(ctx, *req, d_in == d_out), d_scheds, n_scheds, ctx->d_timg, d_in, d_out,
+    const int e = launch_request(*req, request_tile(ctx, *req, d_in == d_out), d_scheds, n_scheds,
+                                 ctx->d_timg, d_in, d_out,
                                  ctx->n_cu, stream);
     if (e)
         return hip_fail((hipError_t)e);
@@ -1747,8 +1762,9 @@ int time_plan(aes_plan *plan, const aes_schedule_t *d_scheds, const uint8_t *d_i
     for (int i = 0; i <= iters && !st; i++) {
         hipError_t e = hipEventRecord(a, ctx->capture);
         if (e == hipSuccess) {
-            st = launch_planned(ctx, view_of(plan->p, plan->d_units, plan->d_units, plan->d_ctrs), d_scheds, plan->n_scheds,
-                                d_in, d_out, ctx->capture);
+            st = launch_planned(ctx,
+                                view_of(plan->p, plan->d_units, plan->d_units, plan->d_ctrs),
+                                d_scheds, plan->n_scheds, d_in, d_out, ctx->capture);
             if (!st)
                 e = hipEventRecord(b, ctx->capture);
         }

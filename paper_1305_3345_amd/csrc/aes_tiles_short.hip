@@ -64,6 +64,76 @@ __global__ __launch_bounds__(BD) void k_tiles_short(
     run_parts<DEC, NB, BD>(lds, fill, n_parts, in == out, record, load, in, out);
 }
 
+// Inclusive sum over the lanes of a wave (zero enters where a row shift or a
+// broadcast has no source).
+__device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t v) {
+#define AESGPU_STEP(CTRL, ROWS) \
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+    AESGPU_STEP(0x111, 0xF)  // row_shr:1, 2, 4, 8
+    AESGPU_STEP(0x112, 0xF)
+    AESGPU_STEP(0x114, 0xF)
+    AESGPU_STEP(0x118, 0xF)
+    AESGPU_STEP(0x142, 0xA)  // row_bcast:15 into rows 1 and 3
+    AESGPU_STEP(0x143, 0xC)  // row_bcast:31 into rows 2 and 3
+#undef AESGPU_STEP
+    return v;
+}
+
+// Encryption-side units of any sizes: every workgroup takes the next `per`
+// units, the first `more` workgroups one more (at most 64), and its waves take
+// their 1 KiB parts in turn, empty ones left out.  The first wave fetches the
+// records for all, through LDS; each wave then holds record `lane` and finds a
+// part's unit with a ballot over the running sum of the parts.
+__global__ __launch_bounds__(1024) void k_tiles_uneven(
+    const Unit *__restrict__ units, uint32_t per, uint32_t more,
+    const uint32_t *__restrict__ timg, const aes_schedule_t *__restrict__ sched, const uint8_t *in,
+    uint32_t n_sched, uint8_t *out) {
+    __shared__ __align__(16) uint32_t lds[LDS_ENC_WORDS + 512u];
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t lo = blockIdx.x * per + (blockIdx.x < more ? blockIdx.x : more);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint4 a = make_uint4(0u, 0u, 0u, 0u), b = a;
+    if (wave == 0u && lane < per + (blockIdx.x < more)) {
+        const uint4 *p = reinterpret_cast<const uint4 *>(units + lo + lane);
+        a = p[0];
+        b = p[1];
+    }
+    const TableFill<false, 1024> fill(timg);
+    __builtin_amdgcn_sched_barrier(0);
+    fill.store(lds);
+    uint4 *rec = reinterpret_cast<uint4 *>(lds + LDS_ENC_WORDS) + 2u * lane;
+    if (wave == 0u) {
+        rec[0] = a;
+        rec[1] = b;
+    }
+    __syncthreads();
+    a = rec[0];
+    b = rec[1];
+    const uint32_t end = wave_prefix_sum((a.z + 1023u) >> 10);
+    const uint32_t n_parts = (uint32_t)__builtin_amdgcn_readlane((int)end, 63);
+    const auto record = [](uint32_t) { return 0; };
+    const auto load = [&](uint32_t i, int, Part<false, 1> &p) {
+        const bool valid = i < n_parts;
+        const uint32_t k = valid ? (uint32_t)__builtin_popcountll(__ballot(end <= i)) : 0u;
+        const auto get = [k](uint32_t v) {
+            return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)k);
+        };
+        Unit un;
+        un.off = (uint64_t)get(a.y) << 32 | get(a.x);
+        un.nbytes = get(a.z);
+        un.meta = get(a.w);
+        un.w[0] = get(b.x);
+        un.w[1] = get(b.y);
+        un.w[2] = get(b.z);
+        un.w[3] = get(b.w);
+        const uint32_t part = valid ? i - (get(end) - ((un.nbytes + 1023u) >> 10)) : 0u;
+        p.load(lane, un, valid, part, nullptr, sched, n_sched, in);
+    };
+    Part<false, 1> cur;
+    load(wave, 0, cur);
+    run_passes<false, 1, 1024>(lds, n_parts, false, cur, record, load, in, out);
+}
+
 // A unit table among the kernel arguments.
 struct InlineUnits {
     Unit u[INLINE_UNITS];
@@ -86,7 +156,8 @@ __global__ __launch_bounds__(256) void k_tiles_inline(
     const auto record = [](uint32_t) { return 0; };
     const auto load = [&](uint32_t k, int, Part<DEC, 1> &p) {
         // The only pass; there is no second one to load.
-        p.load(lane, un, u < n && k < 4u, i & ((1u << parts_log2) - 1u), nullptr, sched, n_sched, in);
+        p.load(lane, un, u < n && k < 4u, i & ((1u << parts_log2) - 1u), nullptr, sched, n_sched,
+               in);
     };
     run_parts<DEC, 1, 256>(lds, fill, 1u, false, record, load, in, out);
 }
@@ -139,7 +210,8 @@ static uint32_t short_waves(uint64_t parts, uint32_t n_wg, uint32_t unit_parts) 
                                : (K)&KERNEL<false, 1, 1024>))
 
 bool launch_tiles_short(bool dec, const Unit *d_units, uint32_t n_units, uint32_t max_bytes,
-                        const aes_schedule_t *d_sched, uint32_t n_sched, const uint32_t *d_timg,
+                        uint64_t kib_parts, const aes_schedule_t *d_sched, uint32_t n_sched,
+                     const uint32_t *d_timg,
                         const void *d_preds, const uint8_t *d_in, uint8_t *d_out, int n_cu,
                         void *stream, int *err) {
     const uint32_t cus = (uint32_t)n_cu < 65535u ? (uint32_t)n_cu : 65535u;
@@ -158,18 +230,27 @@ bool launch_tiles_short(bool dec, const Unit *d_units, uint32_t n_units, uint32_
             break;
     }
     const uint64_t parts = (uint64_t)n_units << lg;
-    if (lg > 4 || (parts > SHORT_PARTS_PER_CU * cus && max_bytes > 1024))
-        return false;
+    if (lg > 4 || (parts > SHORT_PARTS_PER_CU * cus && max_bytes > 1024)) {
+        if (dec || n_units > 64ull * cus || kib_parts >= 2ull * n_units ||
+            kib_parts > UNEVEN_PARTS_PER_CU * (uint64_t)cus)
+            return false;
+        const uint32_t wgs = n_units < cus ? n_units : cus;
+        hipLaunchKernelGGL(k_tiles_uneven, dim3(wgs), dim3(1024), 0, (hipStream_t)stream, d_units,
+                           n_units / wgs, n_units % wgs, d_timg, d_sched, d_in, n_sched, d_out);
+        *err = hipGetLastError();
+        return true;
+    }
     const uint32_t waves = nb == 2 ? 16u : short_waves(parts, cus, 1u << lg);
     const uint32_t per_wg = waves >> lg;  // units of one pass
     uint32_t grid = (n_units + per_wg - 1) / per_wg;
     if (grid > cus)
         grid = cus;
-    using K = void (*)(const Unit *, uint32_t, uint16_t, uint16_t, const uint32_t *, const aes_schedule_t *,
-                       const uint8_t *, uint32_t, const uint4 *, uint8_t *);
+    using K = void (*)(const Unit *, uint32_t, uint16_t, uint16_t, const uint32_t *,
+                       const aes_schedule_t *, const uint8_t *, uint32_t, const uint4 *, uint8_t *);
     const K k = AESGPU_SHORT(k_tiles_short, K, dec, nb, waves);
     hipLaunchKernelGGL(k, dim3(grid), dim3(64 * waves), 0, (hipStream_t)stream, d_units,
-                       n_units / grid, (uint16_t)(n_units % grid), (uint16_t)lg, d_timg, d_sched, d_in, n_sched, (const uint4 *)d_preds, d_out);
+                       n_units / grid, (uint16_t)(n_units % grid), (uint16_t)lg, d_timg, d_sched,
+                       d_in, n_sched, (const uint4 *)d_preds, d_out);
     *err = hipGetLastError();
     return true;
 }
@@ -223,7 +304,8 @@ bool launch_request_short(const aes_req_t &r, const aes_schedule_t *d_sched, uin
     const K k = AESGPU_SHORT(k_request_short, K, dec, nb, waves);
     hipLaunchKernelGGL(k, dim3(grid), dim3(64 * waves), 0, (hipStream_t)stream, d_timg, d_sched,
                        d_in, r.offset, (uint32_t)r.length, r.key_idx | (r.op << META_OP_SHIFT),
-                       (uint32_t)(parts / grid), (uint32_t)(parts % grid), w01, w23, n_sched, d_out);
+                       (uint32_t)(parts / grid), (uint32_t)(parts % grid), w01, w23, n_sched,
+                       d_out);
     *err = hipGetLastError();
     return true;
 }

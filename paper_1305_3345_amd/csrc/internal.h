@@ -85,10 +85,12 @@ struct MixedArgs {
 // aes_tiles_ctr.hip and aes_tiles_dec.hip; the others: aes_kernels.hip.
 // Tile launchers take d_ctrs: TILE_CTRS zeroed per-workgroup counters that
 // every launch leaves zeroed (launches sharing them must not overlap); with
-// zero_ctrs they clear the ones they use first.  max_bytes: the largest unit.
+// zero_ctrs they clear the ones they use first.  max_bytes: the largest unit;
+// kib_parts: the units' parts of 1 KiB (encryption side).
 constexpr uint32_t TILE_CTRS = 65536;
 int launch_ctr_tiles(const Unit *d_units, uint32_t n_units, uint32_t max_bytes,
-                     const aes_schedule_t *d_sched, uint32_t n_sched, const uint32_t *d_timg,
+                     uint64_t kib_parts, const aes_schedule_t *d_sched, uint32_t n_sched,
+                     const uint32_t *d_timg,
                      const uint8_t *d_in, uint8_t *d_out, uint32_t *d_ctrs, bool zero_ctrs,
                      const TileLaunch &cfg, int n_cu, void *stream);
 // Bitsliced CTR (aes_bitslice.hip): units in groups of 8 per wave, worked in
@@ -128,8 +130,16 @@ int launch_request(const aes_req_t &r, uint32_t tile, const aes_schedule_t *d_sc
 // 16.9, 4,096 18.4 and 17.7, 32,768 114 and 93.  In parts of 2 KiB a compute
 // unit, 4,096 such units are 32.
 constexpr uint32_t SHORT_PARTS_PER_CU = 24;
+// Encryption-side units of uneven sizes, by the parts of 1 KiB that they have
+// (kib_parts, fewer than two a unit, up to this many a compute unit): lengths
+// log-uniform to 16 KB, tile kernel against this one, AES-192 CTR 18.1 / 16.0
+// us at 28 parts a compute unit, 23.9 / 20.6 at 42, 29.4 / 23.8 at 55; ECB 14.5
+// / 13.1, 17.7 / 17.1, 23.3 / 20.3.  CBC decryption gained nothing (17.8 / 18.1,
+// 22.3 / 23.3, 29.2 / 27.8), and fuller units lose (4 KiB pages 18.1 / 21.4).
+constexpr uint32_t UNEVEN_PARTS_PER_CU = 64;
 bool launch_tiles_short(bool dec, const Unit *d_units, uint32_t n_units, uint32_t max_bytes,
-                        const aes_schedule_t *d_sched, uint32_t n_sched, const uint32_t *d_timg,
+                        uint64_t kib_parts, const aes_schedule_t *d_sched, uint32_t n_sched,
+                     const uint32_t *d_timg,
                         const void *d_preds, const uint8_t *d_in, uint8_t *d_out, int n_cu,
                         void *stream, int *err);
 // The same for a table in host memory of up to INLINE_UNITS units (none with

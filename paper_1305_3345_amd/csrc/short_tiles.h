@@ -216,32 +216,25 @@ struct Part {
     }
 };
 
-// Runs the parts [0, n_parts) of a workgroup of BD threads, BD / 64 at a time
-// (n_parts > 0, uniform over the workgroup).  unit(i, un): part i's unit
-// record, requested a pass before load(i, un, part) uses it.  in_place: a part
-// may have to read what another part of this workgroup overwrites (CBC
-// decryption): then no wave stores a pass before every wave has loaded the
-// next.
+// The passes of a workgroup of BD threads over its parts [0, n_parts), BD / 64
+// at a time; n_parts is uniform over the workgroup, cur this wave's first part,
+// loaded.  in_place: a part may have to read what another part of this
+// workgroup overwrites (CBC decryption): then no wave stores a pass before
+// every wave has loaded the next.  record(i), load(i, record, part): see
+// run_parts.
 template <bool DEC, int NB, uint32_t BD, class Record, class Load>
-__device__ __forceinline__ void run_parts(uint32_t *lds, const TableFill<DEC, BD> &fill,
-                                          uint32_t n_parts, bool in_place, const Record &record,
-                                          const Load &load, const uint8_t *in, uint8_t *out) {
+__device__ __forceinline__ void run_passes(const uint32_t *lds, uint32_t n_parts, bool in_place,
+                                           Part<DEC, NB> &cur, const Record &record,
+                                           const Load &load, const uint8_t *in, uint8_t *out) {
     const uint32_t lane = threadIdx.x & 63u;
-    uint32_t i = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     constexpr uint32_t STEP = BD / 64u;
-    Part<DEC, NB> cur, nxt;
-    load(i, record(i), cur);
-    auto ahead = record(i + STEP);
-    __builtin_amdgcn_sched_barrier(0);  // all loads are issued before the fill waits for its own
-    fill.store(lds);
-    asm volatile("" ::"v"(cur.kreg));  // loaded above, not where it is used
-    if (DEC)
-        cur.arrived();
-    __syncthreads();
+    uint32_t i = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) + STEP;
+    auto ahead = record(i);
+    Part<DEC, NB> nxt;
     for (uint32_t base = 0; base < n_parts; base += STEP) {
-        i += STEP;
         load(i, ahead, nxt);
-        ahead = record(i + STEP);
+        i += STEP;
+        ahead = record(i);
         const uint32_t nr = cur.round_count();
         const bool run = cur.nbytes && (nr == 10u || nr == 12u || nr == 14u);
         uint32_t o[NB][4];
@@ -255,6 +248,25 @@ __device__ __forceinline__ void run_parts(uint32_t *lds, const TableFill<DEC, BD
             cur.store(lane, o, in, out);
         cur = nxt;
     }
+}
+
+// Fills the tables and runs the parts [0, n_parts) of a workgroup (n_parts >
+// 0).  record(i): part i's unit record, requested a pass before load(i, record,
+// part) uses it.
+template <bool DEC, int NB, uint32_t BD, class Record, class Load>
+__device__ __forceinline__ void run_parts(uint32_t *lds, const TableFill<DEC, BD> &fill,
+                                          uint32_t n_parts, bool in_place, const Record &record,
+                                          const Load &load, const uint8_t *in, uint8_t *out) {
+    const uint32_t i = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    Part<DEC, NB> cur;
+    load(i, record(i), cur);
+    __builtin_amdgcn_sched_barrier(0);  // all loads are issued before the fill waits for its own
+    fill.store(lds);
+    asm volatile("" ::"v"(cur.kreg));  // loaded above, not where it is used
+    if (DEC)
+        cur.arrived();
+    __syncthreads();
+    run_passes<DEC, NB, BD>(lds, n_parts, in_place, cur, record, load, in, out);
 }
 
 }  // namespace aesgpu

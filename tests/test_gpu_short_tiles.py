@@ -149,3 +149,21 @@ def test_units_among_arguments(fresh, op, n, inplace):
             msg = first_mismatch(run_gpu(fresh, wl, inp, form=form, inplace=inplace),
                                  run_oracle(wl, inp, inplace=inplace))
             assert msg is None, f"{form}: {msg}"
+
+
+@pytest.mark.parametrize("op", ["ctr", "ecb_enc"])
+@pytest.mark.parametrize("n,top", [(2600, 16001), (5000, 9000), (9000, 2500)])
+def test_uneven_units(ctx, op, n, top):
+    """Encryption-side units of uneven sizes (log-uniform lengths): a
+    workgroup's units share its waves' parts, over two to four passes."""
+    print(f"[gpu] uneven units: {op}, {n} requests to {top} B", flush=True)
+    lengths = np.exp(np.random.default_rng(n).uniform(0, np.log(top), n)).astype(np.uint64)
+    if op != "ctr":
+        lengths = (lengths + np.uint64(15)) // np.uint64(16) * np.uint64(16)
+    for inplace in (False, True):
+        wl = requests(op, lengths, n)
+        inp = wl.data()
+        for form in ("plan", "batch"):
+            msg = first_mismatch(run_gpu(ctx, wl, inp, form=form, inplace=inplace),
+                                 run_oracle(wl, inp, inplace=inplace))
+            assert msg is None, f"{form} inplace={inplace}: {msg}"
