@@ -211,9 +211,8 @@ static uint32_t short_waves(uint64_t parts, uint32_t n_wg, uint32_t unit_parts) 
 
 bool launch_tiles_short(bool dec, const Unit *d_units, uint32_t n_units, uint32_t max_bytes,
                         uint64_t kib_parts, const aes_schedule_t *d_sched, uint32_t n_sched,
-                     const uint32_t *d_timg,
-                        const void *d_preds, const uint8_t *d_in, uint8_t *d_out, int n_cu,
-                        void *stream, int *err) {
+                        const uint32_t *d_timg, const void *d_preds, const uint8_t *d_in,
+                        uint8_t *d_out, int n_cu, void *stream, int *err) {
     const uint32_t cus = (uint32_t)n_cu < 65535u ? (uint32_t)n_cu : 65535u;
     // One block per lane for one pass, else two.  Units of up to 1 KiB, which
     // fill at most half of a tile kernel's step, run here in any number, one

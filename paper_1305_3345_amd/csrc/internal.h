@@ -139,9 +139,8 @@ constexpr uint32_t SHORT_PARTS_PER_CU = 24;
 constexpr uint32_t UNEVEN_PARTS_PER_CU = 64;
 bool launch_tiles_short(bool dec, const Unit *d_units, uint32_t n_units, uint32_t max_bytes,
                         uint64_t kib_parts, const aes_schedule_t *d_sched, uint32_t n_sched,
-                     const uint32_t *d_timg,
-                        const void *d_preds, const uint8_t *d_in, uint8_t *d_out, int n_cu,
-                        void *stream, int *err);
+                        const uint32_t *d_timg, const void *d_preds, const uint8_t *d_in,
+                        uint8_t *d_out, int n_cu, void *stream, int *err);
 // The same for a table in host memory of up to INLINE_UNITS units (none with
 // FLAG_PRED_IN if d_in == d_out), copied into the kernel's arguments: nothing
 // of it is read after the call.

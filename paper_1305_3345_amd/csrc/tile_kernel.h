@@ -109,10 +109,9 @@ inline TileKernel pick_tile_kernel(int nb, int wg) {
 template <bool DEC>
 inline int launch_tiles(const Unit *d_units, uint32_t n_units, uint32_t max_bytes,
                         uint64_t kib_parts, const aes_schedule_t *d_sched, uint32_t n_sched,
-                     const uint32_t *d_timg,
-                        const void *d_preds, const uint8_t *d_in, uint8_t *d_out,
-                        uint32_t *d_ctrs, bool zero_ctrs, const TileLaunch &cfg, int n_cu,
-                        void *stream) {
+                        const uint32_t *d_timg, const void *d_preds, const uint8_t *d_in,
+                        uint8_t *d_out, uint32_t *d_ctrs, bool zero_ctrs, const TileLaunch &cfg,
+                        int n_cu, void *stream) {
     if (!n_units)
         return hipSuccess;
     // Under the default shape, launches of a few passes take the kernel for
