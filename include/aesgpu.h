@@ -130,9 +130,14 @@ typedef struct aes_req {
 /* Batched service call (paper sections 2 and 3.3: many independent buffers
  * in one GPU launch).  d_scheds: device array of n_scheds schedules.
  * d_in, d_out: device buffers of buf_bytes bytes.  reqs: host array of
- * n_reqs requests, validated and planned on the host, then copied to the
- * device through pinned staging before the call returns.  Work is launched on
- * stream; bytes of d_out outside every request are never written.
+ * n_reqs requests, validated, planned and copied before the call returns (to
+ * kernel arguments, to the device, or to pinned staging that the kernels read).
+ * Work is launched on stream; bytes of d_out outside every request are never
+ * written.  On a stream that is being captured the call is recorded with these
+ * requests, whatever other calls come before a replay: a table that does not
+ * fit the kernel arguments is kept in device memory by the context until it is
+ * destroyed (AES_ERR_NOMEM once a context keeps 4 GiB of them), so a program
+ * that records again and again does better with a plan.
  * Errors: AES_ERR_ARG, AES_ERR_LENGTH, AES_ERR_RANGE, AES_ERR_OVERLAP,
  * AES_ERR_DEVICE, AES_ERR_NOMEM.  A schedule whose nr is not 10, 12 or 14
  * leaves its requests' output bytes unwritten. */
@@ -148,7 +153,9 @@ int aes_batch(aes_ctx_t *ctx, const aes_schedule_t *d_scheds, uint32_t n_scheds,
  * per CBC-encrypt request), the in-place CBC-decrypt predecessor snapshots and
  * the tile counters live in one fixed device array per GPU (about 24.5 MiB,
  * held until the process ends); the requests are planned in fixed host
- * arrays and copied from there before the call returns.  Every call on one
+ * arrays and copied from there before the call returns (on a stream that is
+ * being captured, into the arguments of kernels that write the table at every
+ * replay, 96 units each).  Every call on one
  * GPU shares that GPU's array: calls whose work overlaps in time on one GPU
  * (launched on different streams without ordering, or from several host
  * threads) race on it and must be serialised by the caller; calls on one

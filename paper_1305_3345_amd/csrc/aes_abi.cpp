@@ -498,6 +498,9 @@ struct aes_ctx : LaunchCtx {
     std::vector<aes_req_t> scratch_reqs;
     Planned scratch_plan;
     std::vector<ChainKey> scratch_keys;  // the order of a batch's chains
+    std::vector<Unit> scratch_units;     // unit records of a captured call, before their upload
+    std::vector<void *> captured;        // tables of captured calls (captured_table)
+    size_t captured_bytes = 0;
     std::unique_ptr<HostPool> pool;  // large single-op calls (created on first use)
     hipStream_t copy = nullptr;      // unit-table uploads of the single-call forms
 };
@@ -609,7 +612,6 @@ constexpr size_t DIRECT_UNITS_BYTES = 16384 * sizeof(Unit);
 // ubytes bytes (need = device bytes with the in-place snapshots): waits for
 // the slot's last launch, then grows its pinned and device buffers if needed.
 int take_slot(aes_ctx *ctx, size_t ubytes, size_t need, Slot **out) {
-    HIP_TRY(hipSetDevice(ctx->device));
     Slot &s = ctx->slots[ctx->next_slot];
     ctx->next_slot = (ctx->next_slot + 1) % aes_ctx::N_SLOTS;
     if (s.ev_pending) {
@@ -649,25 +651,21 @@ int take_slot(aes_ctx *ctx, size_t ubytes, size_t need, Slot **out) {
     return AES_OK;
 }
 
-// Makes a slot's unit table ready for a launch on `stream`; *units is where
-// the launch reads it.  A small table is read by the kernels from the pinned
-// staging buffer itself.  A larger one is uploaded: when the stream is not
-// being captured, the copy goes on the context's copy stream and the launch
-// waits for it by event, so the upload of one call overlaps the kernels of the
-// call before; under capture it stays on `stream`.  The slot is free of
+// Makes a slot's unit table ready for a launch on `stream` (not being
+// captured); *units is where the launch reads it.  A small table is read by the
+// kernels from the pinned staging buffer itself.  A larger one is uploaded on
+// the context's copy stream and the launch waits for it by event, so the upload
+// of one call overlaps the kernels of the call before.  The slot is free of
 // earlier uploads and launches (its event was waited for).
 int upload_units(aes_ctx *ctx, Slot &s, size_t ubytes, void *stream, const void **units) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    HIP_TRY(hipStreamIsCapturing((hipStream_t)stream, &cap));
-    *units = s.d_units;
-    if (cap == hipStreamCaptureStatusNone && ubytes <= DIRECT_UNITS_BYTES) {
+    if (ubytes <= DIRECT_UNITS_BYTES) {
         *units = s.d_stage;
         return AES_OK;
     }
-    if (cap == hipStreamCaptureStatusNone && !ctx->copy &&
-        hipStreamCreateWithFlags(&ctx->copy, hipStreamNonBlocking) != hipSuccess)
+    *units = s.d_units;
+    if (!ctx->copy &&
+        hipStreamCreateWithFlags(&ctx->copy, hipStreamNonBlocking) != hipSuccess) {
         ctx->copy = nullptr;
-    if (cap != hipStreamCaptureStatusNone || !ctx->copy) {
         HIP_TRY(hipMemcpyAsync(s.d_units, s.h_stage, ubytes, hipMemcpyHostToDevice,
                                (hipStream_t)stream));
         return AES_OK;
@@ -675,6 +673,59 @@ int upload_units(aes_ctx *ctx, Slot &s, size_t ubytes, void *stream, const void 
     HIP_TRY(hipMemcpyAsync(s.d_units, s.h_stage, ubytes, hipMemcpyHostToDevice, ctx->copy));
     HIP_TRY(hipEventRecord(s.copied, ctx->copy));
     HIP_TRY(hipStreamWaitEvent((hipStream_t)stream, s.copied, 0));
+    return AES_OK;
+}
+
+// Whether `stream` is recording into a graph.
+int is_capturing(void *stream, bool *out) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing((hipStream_t)stream, &cap));
+    *out = cap != hipStreamCaptureStatusNone;
+    return AES_OK;
+}
+
+// The calling thread may allocate and copy while a stream is being captured
+// (on other streams: nothing of it is recorded).
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+// Device memory that one context holds for the calls it recorded, at most.
+constexpr size_t CAPTURED_MAX_BYTES = 4ull << 30;
+
+// The table of a call on a stream that is being captured: device memory of its
+// own, filled here once.  A staging slot would not do: replays come after later
+// calls have taken the slot again.  The context cannot see how long the graph
+// (or an instance of it) lives, so it keeps the table until it is destroyed; a
+// graph needs its context anyway, for the cipher tables.
+int captured_table(aes_ctx *ctx, const Unit *units, size_t n_units, size_t need, PlanView &v) {
+    const size_t ctrs_off = (need + 255) / 256 * 256;
+    const size_t bytes = ctrs_off + 2 * (size_t)TILE_CTRS * sizeof(uint32_t);
+    if (bytes > CAPTURED_MAX_BYTES - ctx->captured_bytes)
+        return AES_ERR_NOMEM;
+    try {
+        ctx->captured.reserve(ctx->captured.size() + 1);
+    } catch (const std::bad_alloc &) {
+        return AES_ERR_NOMEM;
+    }
+    RelaxedCapture relaxed;
+    if (!ctx->copy)
+        HIP_TRY(hipStreamCreateWithFlags(&ctx->copy, hipStreamNonBlocking));
+    uint8_t *d = nullptr;
+    if (hipMalloc((void **)&d, bytes) != hipSuccess)
+        return AES_ERR_NOMEM;
+    ctx->captured.push_back(d);
+    ctx->captured_bytes += bytes;
+    const int e = launch_zero_words((uint32_t *)(d + ctrs_off), 2 * TILE_CTRS, ctx->copy);
+    if (e)
+        return hip_fail((hipError_t)e);
+    HIP_TRY(hipMemcpyAsync(d, units, n_units * sizeof(Unit), hipMemcpyHostToDevice, ctx->copy));
+    HIP_TRY(hipStreamSynchronize(ctx->copy));
+    v.d_units = d;
+    v.d_preds = (Unit *)d + n_units;
+    v.d_ctrs = (uint32_t *)(d + ctrs_off);
     return AES_OK;
 }
 
@@ -810,20 +861,44 @@ void pack_units(const Planned &p, void *dst) {
         memcpy(u, p.chains.data(), p.chains.size() * sizeof(Unit));
 }
 
-// Launches a slot's unit table on `stream` (uploading it if need be) and marks
-// the slot in use until that is done.
-int launch_slot(aes_ctx *ctx, Slot &s, PlanView v, const aes_schedule_t *d_scheds,
-                uint32_t n_scheds, const uint8_t *d_in, uint8_t *d_out, void *stream) {
+// Launches a batch of a plan view without its memory: write(u) puts its unit
+// records at u.  They go through a staging slot, which is in use until the
+// launch is done, or, on a stream that is being captured, into a table of the
+// call's own.
+template <class Write>
+int launch_table(aes_ctx *ctx, PlanView v, const Write &write, const aes_schedule_t *d_scheds,
+                 uint32_t n_scheds, const uint8_t *d_in, uint8_t *d_out, void *stream) {
     const size_t n = v.n_dec + v.n_ctr + v.n_chain;
-    int st = upload_units(ctx, s, n * sizeof(Unit), stream, &v.d_units);
+    const size_t need = units_bytes(v.n_dec, v.n_ctr, v.n_chain);
+    HIP_TRY(hipSetDevice(ctx->device));
+    bool capturing = false;
+    int st = is_capturing(stream, &capturing);
     if (st)
         return st;
-    v.d_preds = (Unit *)s.d_units + n;
-    v.d_ctrs = s.d_ctrs;
+    if (capturing) {
+        try {
+            if (ctx->scratch_units.size() < n)
+                ctx->scratch_units.resize(n);
+        } catch (const std::bad_alloc &) {
+            return AES_ERR_NOMEM;
+        }
+        write(ctx->scratch_units.data());
+        if ((st = captured_table(ctx, ctx->scratch_units.data(), n, need, v)))
+            return st;
+        return launch_planned(ctx, v, d_scheds, n_scheds, d_in, d_out, stream);
+    }
+    Slot *s = nullptr;
+    if ((st = take_slot(ctx, n * sizeof(Unit), need, &s)))
+        return st;
+    write((Unit *)s->h_stage);
+    if ((st = upload_units(ctx, *s, n * sizeof(Unit), stream, &v.d_units)))
+        return st;
+    v.d_preds = (Unit *)s->d_units + n;
+    v.d_ctrs = s->d_ctrs;
     if ((st = launch_planned(ctx, v, d_scheds, n_scheds, d_in, d_out, stream)))
         return st;
-    HIP_TRY(hipEventRecord(s.ev, (hipStream_t)stream));
-    s.ev_pending = true;
+    HIP_TRY(hipEventRecord(s->ev, (hipStream_t)stream));
+    s->ev_pending = true;
     return AES_OK;
 }
 
@@ -896,15 +971,13 @@ int run_batch(aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_scheds,
     } catch (const std::bad_alloc &) {
         return AES_ERR_NOMEM;
     }
-    Slot *s = nullptr;
-    if ((st = take_slot(ctx, n_units * sizeof(Unit), units_bytes(v.n_dec, v.n_ctr, v.n_chain),
-                        &s)))
-        return st;
-    if (group_ctr || group_dec)
-        pack_units(p, s->h_stage);
-    else
-        write_units(reqs, n, tile, b, (Unit *)s->h_stage, ctx->scratch_keys.data());
-    return launch_slot(ctx, *s, v, d_scheds, n_scheds, d_in, d_out, stream);
+    const auto put = [&](Unit *u) {
+        if (group_ctr || group_dec)
+            pack_units(p, u);
+        else
+            write_units(reqs, n, tile, b, u, ctx->scratch_keys.data());
+    };
+    return launch_table(ctx, v, put, d_scheds, n_scheds, d_in, d_out, stream);
 }
 
 // ------------------------------------------------- batches without allocation
@@ -994,10 +1067,20 @@ int run_batch_noalloc(aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_s
         return st;
     // 4. Upload (the static host array is read before the copy call returns,
     //    as for any copy from pageable memory) and launch; a kernel that uses
-    //    the tile counters has them cleared first.
+    //    the tile counters has them cleared first.  A copy that is being
+    //    captured would read the array at every replay, after later calls have
+    //    written theirs to it: there the records go by value, with kernels.
     HIP_TRY(hipSetDevice(ctx->device));
-    HIP_TRY(hipMemcpyAsync(d_scratch, g_noalloc_units, n_units * sizeof(Unit),
-                           hipMemcpyHostToDevice, (hipStream_t)stream));
+    bool capturing = false;
+    if ((st = is_capturing(stream, &capturing)))
+        return st;
+    if (capturing) {
+        if (const int e = launch_put_units(g_noalloc_units, n_units, d_scratch, stream))
+            return hip_fail((hipError_t)e);
+    } else {
+        HIP_TRY(hipMemcpyAsync(d_scratch, g_noalloc_units, n_units * sizeof(Unit),
+                               hipMemcpyHostToDevice, (hipStream_t)stream));
+    }
     v.d_units = d_scratch;
     v.d_preds = (Unit *)d_scratch + n_units;
     v.d_ctrs = (uint32_t *)((uint8_t *)d_scratch + NOALLOC_CTRS_OFF);
@@ -1161,15 +1244,13 @@ int single_tiles(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds, uint
         if (launch_few(ctx, few, v, d_scheds, n_scheds, d_in, d_out, stream, &st))
             return st;
     }
-    Slot *s = nullptr;
-    if ((st = take_slot(ctx, n_tiles * sizeof(Unit), units_bytes(v.n_dec, v.n_ctr, 0), &s)))
-        return st;
-    Unit *out = (Unit *)s->h_stage;
-    run([&](int c) {
-        const uint64_t lo = (uint64_t)c * PAR_CHUNK;
-        write(lo, std::min(n, lo + PAR_CHUNK), out + base[c]);
-    });
-    return launch_slot(ctx, *s, v, d_scheds, n_scheds, d_in, d_out, stream);
+    const auto put = [&](Unit *out) {
+        run([&](int c) {
+            const uint64_t lo = (uint64_t)c * PAR_CHUNK;
+            write(lo, std::min(n, lo + PAR_CHUNK), out + base[c]);
+        });
+    };
+    return launch_table(ctx, v, put, d_scheds, n_scheds, d_in, d_out, stream);
 }
 
 int single_mode(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_scheds,
@@ -1309,6 +1390,8 @@ void aes_ctx_destroy(aes_ctx_t *ctx) {
             if (s.d_ctrs)
                 (void)hipFree(s.d_ctrs);
         }
+        for (void *d : ctx->captured)
+            (void)hipFree(d);
         if (ctx->d_timg)
             (void)hipFree(ctx->d_timg);
         if (ctx->capture)

@@ -2,6 +2,7 @@
 // launch) over the round functions of aes_rounds.h.  The tile kernels live in
 // tile_kernel.h, instantiated by aes_tiles_ctr.hip and aes_tiles_dec.hip.
 #include <hip/hip_runtime.h>
+#include <string.h>
 
 #include "aes_chain.h"
 #include "aes_rounds.h"
@@ -278,6 +279,31 @@ int launch_zero_words(uint32_t *d_words, uint32_t n, void *stream) {
     hipLaunchKernelGGL(k_zero_words, dim3((n + 255) / 256), dim3(256), 0, (hipStream_t)stream,
                        d_words, n);
     return hipGetLastError();
+}
+
+// Unit records by value: what a captured launch holds stays as it was recorded.
+struct __align__(16) UnitBlock {
+    Unit u[96];  // 3 KiB of kernel arguments
+};
+
+__global__ __launch_bounds__(192) void k_put_units(UnitBlock b, uint32_t n_pieces, uint4 *dst) {
+    const uint32_t i = threadIdx.x;
+    if (i < n_pieces)
+        dst[i] = reinterpret_cast<const uint4 *>(b.u)[i];
+}
+
+int launch_put_units(const Unit *units, uint64_t n_units, void *d_units, void *stream) {
+    constexpr uint64_t PER = sizeof(UnitBlock) / sizeof(Unit);
+    for (uint64_t at = 0; at < n_units; at += PER) {
+        const uint64_t n = n_units - at < PER ? n_units - at : PER;
+        UnitBlock b;
+        memcpy(b.u, units + at, n * sizeof(Unit));
+        hipLaunchKernelGGL(k_put_units, dim3(1), dim3(2 * PER), 0, (hipStream_t)stream, b,
+                           (uint32_t)(2 * n), (uint4 *)((Unit *)d_units + at));
+        if (const int e = hipGetLastError())
+            return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace aesgpu

@@ -158,6 +158,11 @@ int launch_snapshot_preds(const Unit *d_units, uint32_t n_units, const uint8_t *
 // Sets n words of device memory to zero with a kernel (a fill that stream
 // capture records as a kernel node, not as a memset node).
 int launch_zero_words(uint32_t *d_words, uint32_t n, void *stream);
+// Writes unit records from host memory to d_units with kernels that carry them
+// as arguments: nothing of `units` is read after the call, also not by the
+// replays of a graph that recorded it (96 records a
+// launch).
+int launch_put_units(const Unit *units, uint64_t n_units, void *d_units, void *stream);
 
 // Records a failing hipError_t for aes_last_hip_error and returns
 // AES_ERR_DEVICE (aes_abi.cpp).
