@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include "internal.h"
+#include "launch_rules.h"
 #include "short_tiles.h"
 
 namespace aesgpu {
@@ -190,15 +191,6 @@ __global__ __launch_bounds__(BD) void k_request_short(
     run_parts<DEC, NB, BD>(lds, fill, hi - lo, in == out, record, load, in, out);
 }
 
-// Waves per workgroup: as few (4, 8 or 16) as hold the parts on n_wg
-// workgroups at once, and a unit's parts.
-static uint32_t short_waves(uint64_t parts, uint32_t n_wg, uint32_t unit_parts) {
-    uint32_t waves = 4;
-    while (waves < 16 && (unit_parts > waves || parts > (uint64_t)waves * n_wg))
-        waves *= 2;
-    return waves;
-}
-
 #define AESGPU_SHORT(KERNEL, K, DEC_, NB_, WAVES_)                                             \
     ((DEC_) ? ((NB_) == 2      ? (K)&KERNEL<true, 2, 1024>                                     \
                : (WAVES_) == 4 ? (K)&KERNEL<true, 1, 256>                                      \
@@ -213,43 +205,23 @@ bool launch_tiles_short(bool dec, const Unit *d_units, uint32_t n_units, uint32_
                         uint64_t kib_parts, const aes_schedule_t *d_sched, uint32_t n_sched,
                         const uint32_t *d_timg, const void *d_preds, const uint8_t *d_in,
                         uint8_t *d_out, int n_cu, void *stream, int *err) {
-    const uint32_t cus = (uint32_t)n_cu < 65535u ? (uint32_t)n_cu : 65535u;
-    // One block per lane for one pass, else two.  Units of up to 1 KiB, which
-    // fill at most half of a tile kernel's step, run here in any number, one
-    // block per lane: 16,384 units of 256 B 17.4 us (AES-128 CTR) against 23.3
-    // there, 65,536 units of 1 KiB 59.3 against 82.8, of 1 to 1,024 B 63.7
-    // against 115.5; of 2 KiB and more the tile kernels are as fast or faster.
-    int nb = 1;
-    uint32_t lg = 0;
-    for (;; nb++) {
-        lg = 0;
-        while (lg < 5 && (uint64_t)max_bytes > ((1024ull * nb) << lg))
-            lg++;
-        if (nb == 2 || ((uint64_t)n_units << lg) <= 16ull * cus || max_bytes <= 1024)
-            break;
-    }
-    const uint64_t parts = (uint64_t)n_units << lg;
-    if (lg > 4 || (parts > SHORT_PARTS_PER_CU * cus && max_bytes > 1024)) {
-        if (dec || n_units > 64ull * cus || kib_parts >= 2ull * n_units ||
-            kib_parts > UNEVEN_PARTS_PER_CU * (uint64_t)cus)
-            return false;
-        const uint32_t wgs = n_units < cus ? n_units : cus;
-        hipLaunchKernelGGL(k_tiles_uneven, dim3(wgs), dim3(1024), 0, (hipStream_t)stream, d_units,
-                           n_units / wgs, n_units % wgs, d_timg, d_sched, d_in, n_sched, d_out);
+    const TileChoice c =
+        choose_tiles(dec, n_units, max_bytes, kib_parts, aligned16(d_in, d_out), (uint32_t)n_cu);
+    if (c.kind == TileKind::TILES)
+        return false;
+    if (c.kind == TileKind::UNEVEN) {
+        hipLaunchKernelGGL(k_tiles_uneven, dim3(c.grid), dim3(64 * c.waves), 0,
+                           (hipStream_t)stream, d_units, n_units / c.grid, n_units % c.grid, d_timg,
+                           d_sched, d_in, n_sched, d_out);
         *err = hipGetLastError();
         return true;
     }
-    const uint32_t waves = nb == 2 ? 16u : short_waves(parts, cus, 1u << lg);
-    const uint32_t per_wg = waves >> lg;  // units of one pass
-    uint32_t grid = (n_units + per_wg - 1) / per_wg;
-    if (grid > cus)
-        grid = cus;
     using K = void (*)(const Unit *, uint32_t, uint16_t, uint16_t, const uint32_t *,
                        const aes_schedule_t *, const uint8_t *, uint32_t, const uint4 *, uint8_t *);
-    const K k = AESGPU_SHORT(k_tiles_short, K, dec, nb, waves);
-    hipLaunchKernelGGL(k, dim3(grid), dim3(64 * waves), 0, (hipStream_t)stream, d_units,
-                       n_units / grid, (uint16_t)(n_units % grid), (uint16_t)lg, d_timg, d_sched,
-                       d_in, n_sched, (const uint4 *)d_preds, d_out);
+    const K k = AESGPU_SHORT(k_tiles_short, K, dec, c.nb, c.waves);
+    hipLaunchKernelGGL(k, dim3(c.grid), dim3(64 * c.waves), 0, (hipStream_t)stream, d_units,
+                       n_units / c.grid, (uint16_t)(n_units % c.grid), (uint16_t)c.parts_log2,
+                       d_timg, d_sched, d_in, n_sched, (const uint4 *)d_preds, d_out);
     *err = hipGetLastError();
     return true;
 }
@@ -261,7 +233,8 @@ bool launch_tiles_inline(bool dec, const Unit *units, uint32_t n_units, uint32_t
     while (lg < 2 && max_bytes > 1024u << lg)
         lg++;
     const uint32_t grid = ((n_units << lg) + 3) / 4;
-    if (n_units > INLINE_UNITS || max_bytes > 1024u << lg || grid > (uint32_t)n_cu)
+    if (n_units > INLINE_UNITS || max_bytes > 1024u << lg || grid > (uint32_t)n_cu ||
+        !aligned16(d_in, d_out))
         return false;
     InlineUnits t;
     memcpy(t.u, units, n_units * sizeof(Unit));
@@ -275,7 +248,7 @@ bool launch_tiles_inline(bool dec, const Unit *units, uint32_t n_units, uint32_t
 bool launch_request_short(const aes_req_t &r, const aes_schedule_t *d_sched, uint32_t n_sched,
                           const uint32_t *d_timg, const uint8_t *d_in, uint8_t *d_out, int n_cu,
                           void *stream, int *err) {
-    if (r.op == AES_OP_CBC_ENC)
+    if (r.op == AES_OP_CBC_ENC || !aligned16(d_in, d_out))
         return false;
     // Decrypted in place with CBC, all parts have to be in one workgroup.
     const uint32_t n_wg = r.op == AES_OP_CBC_DEC && d_in == d_out ? 1u : (uint32_t)n_cu;

@@ -122,21 +122,8 @@ int launch_request(const aes_req_t &r, uint32_t tile, const aes_schedule_t *d_sc
                    uint8_t *d_out, int n_cu, void *stream);
 // Units (decryption or encryption tiles) of at most max_bytes each, or one
 // request by value, by the kernels for short launches (aes_tiles_short.hip).
-// False: too much for them, nothing was launched; else *err is the launch's
-// hipError_t.
-// Where the line lies: microseconds a launch of 4 KiB units, here and with the
-// tile kernels (AES-128 CTR; CBC decryption within 1): 1 to 1,024 units 8 and 9
-// to 15 (the launch call itself takes 7.5), 2,048 11.2 and 16.4, 3,000 14.1 and
-// 16.9, 4,096 18.4 and 17.7, 32,768 114 and 93.  In parts of 2 KiB a compute
-// unit, 4,096 such units are 32.
-constexpr uint32_t SHORT_PARTS_PER_CU = 24;
-// Encryption-side units of uneven sizes, by the parts of 1 KiB that they have
-// (kib_parts, fewer than two a unit, up to this many a compute unit): lengths
-// log-uniform to 16 KB, tile kernel against this one, AES-192 CTR 18.1 / 16.0
-// us at 28 parts a compute unit, 23.9 / 20.6 at 42, 29.4 / 23.8 at 55; ECB 14.5
-// / 13.1, 17.7 / 17.1, 23.3 / 20.3.  CBC decryption gained nothing (17.8 / 18.1,
-// 22.3 / 23.3, 29.2 / 27.8), and fuller units lose (4 KiB pages 18.1 / 21.4).
-constexpr uint32_t UNEVEN_PARTS_PER_CU = 64;
+// False: not for them (launch_rules.h), nothing was launched; else *err is the
+// launch's hipError_t.
 bool launch_tiles_short(bool dec, const Unit *d_units, uint32_t n_units, uint32_t max_bytes,
                         uint64_t kib_parts, const aes_schedule_t *d_sched, uint32_t n_sched,
                         const uint32_t *d_timg, const void *d_preds, const uint8_t *d_in,

@@ -1,0 +1,90 @@
+// launch_rules.h -- the rules that choose a kernel and its shape for a launch,
+// from sizes and alignment alone (host code, no HIP).
+#pragma once
+
+#include <stdint.h>
+
+namespace aesgpu {
+
+// The kernels for short launches read the payload with buffer loads, which
+// may not honour the low bits of an address; the tile kernels' global loads
+// take any base.  (Request offsets are multiples of 16.)
+inline bool aligned16(const void *in, const void *out) {
+    return !(((uintptr_t)in | (uintptr_t)out) & 15u);
+}
+
+// Units of decryption or encryption tiles: by the tile kernels, the kernels for
+// short launches, or (encryption) the kernel for uneven units.
+enum class TileKind { TILES, SHORT, UNEVEN };
+struct TileChoice {
+    TileKind kind = TileKind::TILES;
+    uint32_t nb = 0, parts_log2 = 0;  // SHORT: blocks per lane; parts of nb KiB a unit
+    uint32_t waves = 0, grid = 0;     // waves of a workgroup, workgroups
+};
+
+// Where the line lies: microseconds a launch of 4 KiB units, here and with the
+// tile kernels (AES-128 CTR; CBC decryption within 1): 1 to 1,024 units 8 and 9
+// to 15 (the launch call itself takes 7.5), 2,048 11.2 and 16.4, 3,000 14.1 and
+// 16.9, 4,096 18.4 and 17.7, 32,768 114 and 93.  In parts of 2 KiB a compute
+// unit, 4,096 such units are 32.
+constexpr uint32_t SHORT_PARTS_PER_CU = 24;
+// Encryption-side units of uneven sizes, by the parts of 1 KiB that they have
+// (kib_parts, fewer than two a unit, up to this many a compute unit): lengths
+// log-uniform to 16 KB, tile kernel against this one, AES-192 CTR 18.1 / 16.0
+// us at 28 parts a compute unit, 23.9 / 20.6 at 42, 29.4 / 23.8 at 55; ECB 14.5
+// / 13.1, 17.7 / 17.1, 23.3 / 20.3.  CBC decryption gained nothing (17.8 / 18.1,
+// 22.3 / 23.3, 29.2 / 27.8), and fuller units lose (4 KiB pages 18.1 / 21.4).
+constexpr uint32_t UNEVEN_PARTS_PER_CU = 64;
+
+// Waves per workgroup: as few (4, 8 or 16) as hold the parts on n_wg
+// workgroups at once, and a unit's parts.
+inline uint32_t short_waves(uint64_t parts, uint32_t n_wg, uint32_t unit_parts) {
+    uint32_t waves = 4;
+    while (waves < 16 && (unit_parts > waves || parts > (uint64_t)waves * n_wg))
+        waves *= 2;
+    return waves;
+}
+
+// n_units units of at most max_bytes each, with kib_parts parts of 1 KiB in all
+// (encryption side), on n_cu compute units.
+inline TileChoice choose_tiles(bool dec, uint32_t n_units, uint32_t max_bytes,
+                               uint64_t kib_parts, bool aligned, uint32_t n_cu) {
+    TileChoice c;
+    if (!aligned)
+        return c;
+    const uint32_t cus = n_cu < 65535u ? n_cu : 65535u;
+    // One block per lane for one pass, else two.  Units of up to 1 KiB, which
+    // fill at most half of a tile kernel's step, run here in any number, one
+    // block per lane: 16,384 units of 256 B 17.4 us (AES-128 CTR) against 23.3
+    // there, 65,536 units of 1 KiB 59.3 against 82.8, of 1 to 1,024 B 63.7
+    // against 115.5; of 2 KiB and more the tile kernels are as fast or faster.
+    uint32_t nb = 1, lg = 0;
+    for (;; nb++) {
+        lg = 0;
+        while (lg < 5 && (uint64_t)max_bytes > ((1024ull * nb) << lg))
+            lg++;
+        if (nb == 2 || ((uint64_t)n_units << lg) <= 16ull * cus || max_bytes <= 1024)
+            break;
+    }
+    const uint64_t parts = (uint64_t)n_units << lg;
+    if (lg > 4 || (parts > SHORT_PARTS_PER_CU * cus && max_bytes > 1024)) {
+        if (dec || n_units > 64ull * cus || kib_parts >= 2ull * n_units ||
+            kib_parts > UNEVEN_PARTS_PER_CU * (uint64_t)cus)
+            return c;
+        c.kind = TileKind::UNEVEN;
+        c.waves = 16;
+        c.grid = n_units < cus ? n_units : cus;
+        return c;
+    }
+    c.kind = TileKind::SHORT;
+    c.nb = nb;
+    c.parts_log2 = lg;
+    c.waves = nb == 2 ? 16u : short_waves(parts, cus, 1u << lg);
+    const uint32_t per_wg = c.waves >> lg;  // units of one pass
+    c.grid = (n_units + per_wg - 1) / per_wg;
+    if (c.grid > cus)
+        c.grid = cus;
+    return c;
+}
+
+}  // namespace aesgpu

@@ -1,0 +1,59 @@
+"""The rules that choose a kernel for a launch (csrc/launch_rules.h), compiled
+for the host alone: no GPU and no library needed."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SHIM = r"""
+#include "launch_rules.h"
+using namespace aesgpu;
+extern "C" int aligned(uint64_t in, uint64_t out) {
+    return aligned16((const void *)in, (const void *)out);
+}
+extern "C" void choose(int dec, uint32_t n, uint32_t max_bytes, uint64_t kib, int ok,
+                       uint32_t n_cu, uint32_t *out) {
+    const TileChoice c = choose_tiles(dec, n, max_bytes, kib, ok, n_cu);
+    out[0] = (uint32_t)c.kind;
+    out[1] = c.nb;
+    out[2] = c.parts_log2;
+    out[3] = c.waves;
+    out[4] = c.grid;
+}
+"""
+TILES, SHORT, UNEVEN = 0, 1, 2
+CUS = 256
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    src, so = d / "rules.cpp", d / "rules.so"
+    src.write_text(SHIM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC",
+                    "-I" + os.path.join(ROOT, "paper_1305_3345_amd", "csrc"), str(src), "-o",
+                    str(so)], check=True)
+    return ctypes.CDLL(str(so))
+
+
+def choose(rules, lengths, dec=False, ok=True, cus=CUS):
+    """(kind, blocks per lane, log2 parts, waves, workgroups) for units of these bytes."""
+    out = (ctypes.c_uint32 * 5)()
+    kib = 2**64 - 1 if dec else sum((v + 1023) // 1024 for v in lengths)
+    rules.choose(int(dec), len(lengths), max(lengths), ctypes.c_uint64(kib), int(ok), cus, out)
+    return tuple(out)
+
+
+@pytest.mark.parametrize("dec", [False, True])
+@pytest.mark.parametrize("lengths", [[4096], [16] * 5000, [2048] * 3000, [64, 4096] * 3000])
+def test_unaligned_buffers_take_the_tile_kernels(rules, lengths, dec):
+    """Only global loads may read a payload whose base is not 16-byte aligned."""
+    for shift in (1, 2, 4, 8, 15):
+        for a, b in ((shift, 0), (0, shift), (shift, shift)):
+            ok = rules.aligned(ctypes.c_uint64(0x7F0000001000 + a),
+                               ctypes.c_uint64(0x7F0000002000 + b))
+            assert not ok
+            assert choose(rules, lengths, dec, ok)[0] == TILES
+    assert rules.aligned(ctypes.c_uint64(0x7F0000001010), ctypes.c_uint64(0x7F0000002000))
