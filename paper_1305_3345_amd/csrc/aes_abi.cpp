@@ -21,6 +21,7 @@
 
 #include "host_pool.h"
 #include "internal.h"
+#include "launch_rules.h"
 #include "tune_cache.h"
 
 using namespace aesgpu;
@@ -124,6 +125,7 @@ bool is_enc_tile_op(uint32_t op) { return op == AES_OP_CTR || op == AES_OP_ECB_E
 struct BatchScan {
     uint64_t units[5] = {0, 0, 0, 0, 0}, bytes[5] = {0, 0, 0, 0, 0}, kib[5] = {0, 0, 0, 0, 0};
     uint64_t longest = 0;  // bytes of the longest request with tiles
+    uint64_t longest_chain = 0;
     bool sorted = true, overlap = false, pred_in = false;
     uint64_t n_dec() const { return units[AES_OP_CBC_DEC] + units[AES_OP_ECB_DEC]; }
     uint64_t n_enc() const { return units[AES_OP_CTR] + units[AES_OP_ECB_ENC]; }
@@ -143,7 +145,7 @@ inline uint64_t tile_count(uint64_t len, uint32_t tile) {
 // The per-request rules of validate, in its order of errors.
 int scan_requests(const aes_req_t *reqs, uint64_t n, uint32_t n_scheds, uint64_t buf_bytes,
                   uint32_t tile, BatchScan &b) {
-    uint64_t last_off = 0, end = 0, longest = 0;
+    uint64_t last_off = 0, end = 0, longest = 0, longest_chain = 0;
     bool sorted = true, overlap = false, pred_in = false;
     for (uint64_t i = 0; i < n; i++) {
         const aes_req_t &r = reqs[i];
@@ -162,6 +164,7 @@ int scan_requests(const aes_req_t *reqs, uint64_t n, uint32_t n_scheds, uint64_t
         b.kib[r.op] += kib_parts(r.length);
         if (r.op == AES_OP_CBC_ENC) {
             b.units[r.op]++;
+            longest_chain = std::max(longest_chain, r.length);
             continue;
         }
         longest = std::max(longest, r.length);
@@ -170,6 +173,7 @@ int scan_requests(const aes_req_t *reqs, uint64_t n, uint32_t n_scheds, uint64_t
         pred_in |= r.op == AES_OP_CBC_DEC && t > 1;
     }
     b.longest = longest;
+    b.longest_chain = longest_chain;
     b.sorted = sorted;
     b.overlap = overlap;
     b.pred_in = pred_in;
@@ -538,7 +542,8 @@ struct PlanView {
     size_t n_dec, n_ctr, n_chain;
     bool pred_in;
     uint64_t dec_bytes, ctr_bytes;
-    uint32_t max_bytes;  // no tile is larger
+    uint32_t longest_chain;  // bytes
+    uint32_t max_bytes;      // no tile is larger
     uint64_t enc_kib;  // parts of 1 KiB of the encryption tiles
     size_t n_ecb;  // ECB-encrypt tiles: the last n_ecb of the n_ctr encryption tiles
     bool zero_ctrs;  // the counters may not be zero: clear what a launch uses first
@@ -549,7 +554,8 @@ struct PlanView {
 PlanView view_of(const Planned &p, const void *units, void *d_units, uint32_t *d_ctrs) {
     return PlanView{units, (Unit *)d_units + (p.dec.size() + p.ctr.size() + p.chains.size()),
                     d_ctrs, p.dec.size(), p.ctr.size(), p.chains.size(), p.dec_has_pred_in,
-                    p.dec_bytes, p.ctr_bytes, p.max_tile, p.enc_kib, p.n_ecb, false};
+                    p.dec_bytes, p.ctr_bytes, p.chains.empty() ? 0u : p.chains[0].nbytes,
+                    p.max_tile, p.enc_kib, p.n_ecb, false};
 }
 
 }  // namespace
@@ -804,10 +810,9 @@ int launch_planned(const LaunchCtx *ctx, const PlanView &v, const aes_schedule_t
                                    : v.ctr_bytes;
         a.n_dec_wg = dec_workgroups(fused, grid);
         a.chain_lanes = (uint32_t)ctx->chain.lanes;
-        // k_mixed gives chains half of the encryption waves when there are
-        // encryption tiles too, else all of them.
-        a.chain_width = (uint32_t)chain_lanes_for(
-            a.n_chain, ctx->chain.quad, (n_ctr_tab ? 8u : 16u) * ((uint32_t)grid - a.n_dec_wg));
+        a.chain_width = (uint32_t)mixed_chain_lanes(a.n_chain, v.longest_chain, ctx->chain.quad,
+                                                    (uint32_t)grid - a.n_dec_wg,
+                                                    std::max<uint64_t>(fused.ctr_bytes, n_ctr_tab));
         if ((e = launch_mixed(a, ctx->mixed_nb, grid, stream)))
             return hip_fail((hipError_t)e);
         return AES_OK;
@@ -911,6 +916,7 @@ PlanView view_of(const BatchScan &b, uint32_t tile) {
     v.pred_in = b.pred_in;
     v.dec_bytes = b.dec_bytes();
     v.ctr_bytes = b.enc_bytes();
+    v.longest_chain = (uint32_t)b.longest_chain;
     v.max_bytes = (uint32_t)std::min<uint64_t>(tile, b.longest);
     v.enc_kib = b.kib[AES_OP_CTR] + b.kib[AES_OP_ECB_ENC];
     v.n_ecb = b.units[AES_OP_ECB_ENC];

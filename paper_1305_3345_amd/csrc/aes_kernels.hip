@@ -7,6 +7,7 @@
 #include "aes_chain.h"
 #include "aes_rounds.h"
 #include "internal.h"
+#include "launch_rules.h"
 
 namespace aesgpu {
 
@@ -174,12 +175,6 @@ __global__ void k_snapshot_preds(const Unit *__restrict__ units, uint32_t n_unit
 }
 
 // --------------------------------------------------------------- launchers
-
-int chain_lanes_for(uint32_t n_chain, bool grouped, uint32_t max_waves) {
-    if (!grouped)
-        return 1;
-    return n_chain <= 4ull * max_waves ? 16 : 4;
-}
 
 int launch_cbcenc_chains(const Unit *d_units, uint32_t n_units, const aes_schedule_t *d_sched,
                          uint32_t n_sched, const uint32_t *d_timg, const uint8_t *d_in,

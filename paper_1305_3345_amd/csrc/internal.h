@@ -52,17 +52,9 @@ inline bool is_default(const TileLaunch &t) {
 struct ChainLaunch {
     int wg_threads = 256;
     int lanes = 64;     // active lanes (chains) per wave, one lane per chain
-    bool quad = false;  // instead: 16 or 4 lanes per chain (chain_lanes_for)
+    bool quad = false;  // instead: 16 or 4 lanes per chain (launch_rules.h)
     int grid = 0;       // 0 = as many as the chains need, at most one per compute unit
 };
-// Lanes per chain of a launch over n_chain chains that can put max_waves waves
-// on the device for them: 1 unless `grouped`; 16 while every chain then runs
-// at once, four chains to a wave; else 4.  A chain on 16 lanes is 1.2 to 1.3
-// times as fast while a SIMD holds up to three such waves and no slower with
-// four (16,384 chains of 16 KiB, all compute units: 502 against 514 us for
-// AES-128, 674 against 686 us for AES-256; 4,096 chains: 399 against 489 us,
-// 540 against 669 us); a second pass over the chains would double the time.
-int chain_lanes_for(uint32_t n_chain, bool grouped, uint32_t max_waves);
 
 // Arguments of the fused mixed-batch kernel (one launch for all three ops).
 struct MixedArgs {
@@ -78,7 +70,7 @@ struct MixedArgs {
     uint32_t n_sched;
     uint32_t n_dec_wg;      // workgroups [0, n_dec_wg) hold the decryption tables
     uint32_t chain_lanes;   // active lanes per chain wave (one lane per chain)
-    uint32_t chain_width;   // lanes per chain: 1, 4 or 16 (chain_lanes_for)
+    uint32_t chain_width;   // lanes per chain: 1, 4 or 16 (mixed_chain_lanes)
 };
 
 // Host-side launchers.  Each returns a hipError_t value.  Tile kernels:

@@ -87,4 +87,36 @@ inline TileChoice choose_tiles(bool dec, uint32_t n_units, uint32_t max_bytes,
     return c;
 }
 
+// Lanes per chain of a launch over n_chain chains that can put max_waves waves
+// on the device for them: 1 unless `grouped`; 16 while every chain then runs
+// at once, four chains to a wave; else 4.  A chain on 16 lanes is 1.2 to 1.3
+// times as fast while a SIMD holds up to three such waves and no slower with
+// four (16,384 chains of 16 KiB, all compute units: 502 against 514 us for
+// AES-128, 674 against 686 us for AES-256; 4,096 chains: 399 against 489 us,
+// 540 against 669 us); a second pass over the chains would double the time.
+inline int chain_lanes_for(uint32_t n_chain, bool grouped, uint32_t max_waves) {
+    if (!grouped)
+        return 1;
+    return n_chain <= 4ull * max_waves ? 16 : 4;
+}
+
+// The same for chains (the longest of `longest` bytes) that share n_wg
+// workgroups of sixteen waves with encryption tiles of tile_bytes in all; with
+// tiles they get up to half of the waves, and a wave that ends its chains takes
+// no tiles.  So sixteen lanes, which take four times the waves, are right only
+// where the chains are what the launch waits for.  On four lanes a chain works
+// at about 1/156 of the rate of a compute unit's tiles (34 MB/s against 5.3
+// GB/s for AES-128; both scale with the rounds).  Microseconds on four and on
+// sixteen lanes: 8,192 chains of 64, 512 and 2,048 B beside 256 MiB of CTR 197 /
+// 225, 198 / 230, 201 / 241 and beside 16 MiB 17.6 / 19.3, 23.2 / 23.7, 67.5 /
+// 56.3; 2,048 chains of 512 and 8,192 B beside 256 MiB 186 / 197, 272 / 210.
+constexpr uint32_t CHAIN_TILE_RATE = 156;
+inline int mixed_chain_lanes(uint32_t n_chain, uint32_t longest, bool grouped, uint32_t n_wg,
+                             uint64_t tile_bytes) {
+    const int w = chain_lanes_for(n_chain, grouped, (tile_bytes ? 8u : 16u) * n_wg);
+    if (w == 16 && (uint64_t)longest * n_wg * CHAIN_TILE_RATE < tile_bytes)
+        return 4;
+    return w;
+}
+
 }  // namespace aesgpu

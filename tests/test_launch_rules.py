@@ -22,6 +22,10 @@ extern "C" void choose(int dec, uint32_t n, uint32_t max_bytes, uint64_t kib, in
     out[3] = c.waves;
     out[4] = c.grid;
 }
+extern "C" int mixed_lanes(uint32_t n, uint32_t longest, int grouped, uint32_t n_wg,
+                           uint64_t tile_bytes) {
+    return mixed_chain_lanes(n, longest, grouped, n_wg, tile_bytes);
+}
 """
 TILES, SHORT, UNEVEN = 0, 1, 2
 CUS = 256
@@ -57,3 +61,17 @@ def test_unaligned_buffers_take_the_tile_kernels(rules, lengths, dec):
             assert not ok
             assert choose(rules, lengths, dec, ok)[0] == TILES
     assert rules.aligned(ctypes.c_uint64(0x7F0000001010), ctypes.c_uint64(0x7F0000002000))
+
+
+@pytest.mark.parametrize("n,longest,n_wg,mib,lanes", [
+    # What was measured faster on 256 compute units (or the same: few chains).
+    (8192, 64, 256, 256, 4), (8192, 512, 256, 256, 4), (8192, 2048, 256, 256, 4),
+    (2048, 512, 256, 256, 4), (2048, 8192, 256, 256, 16), (8192, 64, 256, 16, 4),
+    (8192, 2048, 256, 16, 16), (2048, 2048, 256, 64, 16), (8192, 512, 256, 64, 4),
+    (500, 262144, 192, 90, 16),  # an uneven mix of requests: the long chains decide
+    # No tiles beside the chains, and more chains than run at once.
+    (64, 16, 1, 0, 16), (65, 16, 1, 0, 4), (8193, 1 << 20, 256, 16, 4)])
+def test_chains_beside_tiles(rules, n, longest, n_wg, mib, lanes):
+    got = rules.mixed_lanes(n, longest, 1, n_wg, ctypes.c_uint64(mib << 20))
+    assert got == lanes
+    assert rules.mixed_lanes(n, longest, 0, n_wg, ctypes.c_uint64(mib << 20)) == 1
