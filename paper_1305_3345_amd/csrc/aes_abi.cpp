@@ -542,6 +542,7 @@ struct PlanView {
     size_t n_dec, n_ctr, n_chain;
     bool pred_in;
     uint64_t dec_bytes, ctr_bytes;
+    uint64_t chain_bytes;
     uint32_t longest_chain;  // bytes
     uint32_t max_bytes;      // no tile is larger
     uint64_t enc_kib;  // parts of 1 KiB of the encryption tiles
@@ -554,7 +555,7 @@ struct PlanView {
 PlanView view_of(const Planned &p, const void *units, void *d_units, uint32_t *d_ctrs) {
     return PlanView{units, (Unit *)d_units + (p.dec.size() + p.ctr.size() + p.chains.size()),
                     d_ctrs, p.dec.size(), p.ctr.size(), p.chains.size(), p.dec_has_pred_in,
-                    p.dec_bytes, p.ctr_bytes, p.chains.empty() ? 0u : p.chains[0].nbytes,
+                    p.dec_bytes, p.ctr_bytes, p.chain_bytes, p.chains.empty() ? 0u : p.chains[0].nbytes,
                     p.max_tile, p.enc_kib, p.n_ecb, false};
 }
 
@@ -810,9 +811,9 @@ int launch_planned(const LaunchCtx *ctx, const PlanView &v, const aes_schedule_t
                                    : v.ctr_bytes;
         a.n_dec_wg = dec_workgroups(fused, grid);
         a.chain_lanes = (uint32_t)ctx->chain.lanes;
-        a.chain_width = (uint32_t)mixed_chain_lanes(a.n_chain, v.longest_chain, ctx->chain.quad,
-                                                    (uint32_t)grid - a.n_dec_wg,
-                                                    std::max<uint64_t>(fused.ctr_bytes, n_ctr_tab));
+        a.chain_width = (uint32_t)mixed_chain_lanes(
+            a.n_chain, v.longest_chain, v.chain_bytes, ctx->chain.quad, (uint32_t)grid - a.n_dec_wg,
+            std::max<uint64_t>(fused.ctr_bytes, n_ctr_tab));
         if ((e = launch_mixed(a, ctx->mixed_nb, grid, stream)))
             return hip_fail((hipError_t)e);
         return AES_OK;
@@ -825,7 +826,7 @@ int launch_planned(const LaunchCtx *ctx, const PlanView &v, const aes_schedule_t
                               n_scheds, ctx->d_timg, d_in, d_out, v.d_ctrs + TILE_CTRS,
                               v.zero_ctrs, ctx->tile_ctr, ctx->n_cu, stream)))
         return hip_fail((hipError_t)e);
-    if ((e = launch_cbcenc_chains(u_chain, (uint32_t)v.n_chain, d_scheds, n_scheds, ctx->d_timg,
+    if ((e = launch_cbcenc_chains(u_chain, (uint32_t)v.n_chain, v.longest_chain, v.chain_bytes, d_scheds, n_scheds, ctx->d_timg,
                                   d_in, d_out, ctx->chain, ctx->n_cu, stream)))
         return hip_fail((hipError_t)e);
     return AES_OK;
@@ -916,6 +917,7 @@ PlanView view_of(const BatchScan &b, uint32_t tile) {
     v.pred_in = b.pred_in;
     v.dec_bytes = b.dec_bytes();
     v.ctr_bytes = b.enc_bytes();
+    v.chain_bytes = b.bytes[AES_OP_CBC_ENC];
     v.longest_chain = (uint32_t)b.longest_chain;
     v.max_bytes = (uint32_t)std::min<uint64_t>(tile, b.longest);
     v.enc_kib = b.kib[AES_OP_CTR] + b.kib[AES_OP_ECB_ENC];

@@ -176,13 +176,14 @@ __global__ void k_snapshot_preds(const Unit *__restrict__ units, uint32_t n_unit
 
 // --------------------------------------------------------------- launchers
 
-int launch_cbcenc_chains(const Unit *d_units, uint32_t n_units, const aes_schedule_t *d_sched,
+int launch_cbcenc_chains(const Unit *d_units, uint32_t n_units, uint32_t longest, uint64_t bytes,
+                         const aes_schedule_t *d_sched,
                          uint32_t n_sched, const uint32_t *d_timg, const uint8_t *d_in,
                          uint8_t *d_out, const ChainLaunch &cfg, int n_cu, void *stream) {
     if (!n_units)
         return hipSuccess;
     const uint32_t cl = cfg.lanes < 1 ? 64u : (cfg.lanes > 64 ? 64u : (uint32_t)cfg.lanes);
-    const int w = chain_lanes_for(n_units, cfg.quad, 16u * (uint32_t)n_cu);
+    const int w = chain_lanes_for(n_units, longest, bytes, cfg.quad, 16u * (uint32_t)n_cu);
     const uint32_t per_wave = w == 1 ? cl : 64u / (uint32_t)w;
     const uint32_t need = (uint32_t)(((uint64_t)n_units + per_wave - 1) / per_wave);
     // Waves of a workgroup (one per compute unit) that run chains: at most.

@@ -102,7 +102,9 @@ int launch_cbcdec_tiles(const Unit *d_units, uint32_t n_units, uint32_t max_byte
                         const void *d_preds, const uint8_t *d_in, uint8_t *d_out,
                         uint32_t *d_ctrs, bool zero_ctrs, const TileLaunch &cfg, int n_cu,
                         void *stream);
-int launch_cbcenc_chains(const Unit *d_units, uint32_t n_units, const aes_schedule_t *d_sched,
+// longest, bytes: of the longest chain, of all.
+int launch_cbcenc_chains(const Unit *d_units, uint32_t n_units, uint32_t longest, uint64_t bytes,
+                         const aes_schedule_t *d_sched,
                          uint32_t n_sched, const uint32_t *d_timg, const uint8_t *d_in,
                          uint8_t *d_out, const ChainLaunch &cfg, int n_cu, void *stream);
 // One launch over a mixed batch (nb = 1 or 2; 1024-thread workgroups).

@@ -87,17 +87,26 @@ inline TileChoice choose_tiles(bool dec, uint32_t n_units, uint32_t max_bytes,
     return c;
 }
 
-// Lanes per chain of a launch over n_chain chains that can put max_waves waves
-// on the device for them: 1 unless `grouped`; 16 while every chain then runs
-// at once, four chains to a wave; else 4.  A chain on 16 lanes is 1.2 to 1.3
-// times as fast while a SIMD holds up to three such waves and no slower with
-// four (16,384 chains of 16 KiB, all compute units: 502 against 514 us for
-// AES-128, 674 against 686 us for AES-256; 4,096 chains: 399 against 489 us,
-// 540 against 669 us); a second pass over the chains would double the time.
-inline int chain_lanes_for(uint32_t n_chain, bool grouped, uint32_t max_waves) {
+// Lanes per chain of a launch over n_chain chains (the longest of `longest`
+// bytes, `bytes` in all) that can put max_waves waves on the device for them: 1
+// unless `grouped`; 16 while every chain then runs at once, four chains to a
+// wave; else 4, as a second pass over the chains would double the time.  A chain
+// on 16 lanes is 1.1 to 1.3 times as fast while a SIMD holds up to three such
+// waves.  With four it is as fast only where the chains are long, or of such
+// lengths that most end early (together no more than three quarters of the
+// slots would hold at the longest length).  Microseconds on four and on sixteen
+// lanes, 256 compute units, AES-128: 12,288 chains of 256, 1,024 and 4,096 B 13.2
+// / 12.9, 36.9 / 34.2, 129 / 116; 16,384 of them 12.2 / 13.0, 36.8 / 38.8, 126 /
+// 130, of 8 and 16 KiB 249 / 250 and 502 / 490 (AES-256 340 / 335, 679 / 662),
+// log-uniform from 16 B to 16 KiB 466 / 377; 13,000 to 14,336 chains alike.
+constexpr uint32_t LONG_CHAIN_BYTES = 8192;
+inline int chain_lanes_for(uint32_t n_chain, uint32_t longest, uint64_t bytes, bool grouped,
+                           uint32_t max_waves) {
     if (!grouped)
         return 1;
-    return n_chain <= 4ull * max_waves ? 16 : 4;
+    if (n_chain > 4ull * max_waves)
+        return 4;
+    return longest >= LONG_CHAIN_BYTES || bytes <= 3ull * max_waves * longest ? 16 : 4;
 }
 
 // The same for chains (the longest of `longest` bytes) that share n_wg
@@ -111,9 +120,10 @@ inline int chain_lanes_for(uint32_t n_chain, bool grouped, uint32_t max_waves) {
 // 225, 198 / 230, 201 / 241 and beside 16 MiB 17.6 / 19.3, 23.2 / 23.7, 67.5 /
 // 56.3; 2,048 chains of 512 and 8,192 B beside 256 MiB 186 / 197, 272 / 210.
 constexpr uint32_t CHAIN_TILE_RATE = 156;
-inline int mixed_chain_lanes(uint32_t n_chain, uint32_t longest, bool grouped, uint32_t n_wg,
-                             uint64_t tile_bytes) {
-    const int w = chain_lanes_for(n_chain, grouped, (tile_bytes ? 8u : 16u) * n_wg);
+inline int mixed_chain_lanes(uint32_t n_chain, uint32_t longest, uint64_t bytes, bool grouped,
+                             uint32_t n_wg, uint64_t tile_bytes) {
+    const int w = tile_bytes ? chain_lanes_for(n_chain, longest, 0, grouped, 8u * n_wg)
+                             : chain_lanes_for(n_chain, longest, bytes, grouped, 16u * n_wg);
     if (w == 16 && (uint64_t)longest * n_wg * CHAIN_TILE_RATE < tile_bytes)
         return 4;
     return w;

@@ -24,7 +24,10 @@ extern "C" void choose(int dec, uint32_t n, uint32_t max_bytes, uint64_t kib, in
 }
 extern "C" int mixed_lanes(uint32_t n, uint32_t longest, int grouped, uint32_t n_wg,
                            uint64_t tile_bytes) {
-    return mixed_chain_lanes(n, longest, grouped, n_wg, tile_bytes);
+    return mixed_chain_lanes(n, longest, (uint64_t)n * longest, grouped, n_wg, tile_bytes);
+}
+extern "C" int lanes(uint32_t n, uint32_t longest, uint64_t bytes, int grouped, uint32_t waves) {
+    return chain_lanes_for(n, longest, bytes, grouped, waves);
 }
 """
 TILES, SHORT, UNEVEN = 0, 1, 2
@@ -70,8 +73,20 @@ def test_unaligned_buffers_take_the_tile_kernels(rules, lengths, dec):
     (8192, 2048, 256, 16, 16), (2048, 2048, 256, 64, 16), (8192, 512, 256, 64, 4),
     (500, 262144, 192, 90, 16),  # an uneven mix of requests: the long chains decide
     # No tiles beside the chains, and more chains than run at once.
-    (64, 16, 1, 0, 16), (65, 16, 1, 0, 4), (8193, 1 << 20, 256, 16, 4)])
+    (48, 16, 1, 0, 16), (65, 16, 1, 0, 4), (8193, 1 << 20, 256, 16, 4)])
 def test_chains_beside_tiles(rules, n, longest, n_wg, mib, lanes):
     got = rules.mixed_lanes(n, longest, 1, n_wg, ctypes.c_uint64(mib << 20))
     assert got == lanes
     assert rules.mixed_lanes(n, longest, 0, n_wg, ctypes.c_uint64(mib << 20)) == 1
+
+
+@pytest.mark.parametrize("n,longest,mean,lanes", [
+    (4096, 64, 64, 16), (12288, 256, 256, 16), (12288, 4096, 4096, 16),
+    (12289, 256, 256, 4), (16384, 4096, 4096, 4), (16384, 1024, 1024, 4),
+    (13312, 8192, 8192, 16), (16384, 65536, 65536, 16),  # long chains
+    (16384, 8192, 1000, 16),  # most end early
+    (16385, 16384, 16384, 4), (65536, 64, 64, 4)])  # more than run at once
+def test_chains_alone(rules, n, longest, mean, lanes):
+    """What was measured faster on 256 compute units of sixteen waves."""
+    assert rules.lanes(n, longest, ctypes.c_uint64(n * mean), 1, 16 * CUS) == lanes
+    assert rules.lanes(n, longest, ctypes.c_uint64(n * mean), 0, 16 * CUS) == 1
