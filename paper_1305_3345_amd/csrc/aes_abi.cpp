@@ -21,7 +21,6 @@
 
 #include "host_pool.h"
 #include "internal.h"
-#include "launch_rules.h"
 #include "tune_cache.h"
 
 using namespace aesgpu;
@@ -123,7 +122,8 @@ bool is_enc_tile_op(uint32_t op) { return op == AES_OP_CTR || op == AES_OP_ECB_E
 // and bytes by operation, and whether the nonempty requests come in offset
 // order without overlapping.
 struct BatchScan {
-    uint64_t units[5] = {0, 0, 0, 0, 0}, bytes[5] = {0, 0, 0, 0, 0}, kib[5] = {0, 0, 0, 0, 0};
+    uint64_t units[5] = {0, 0, 0, 0, 0}, bytes[5] = {0, 0, 0, 0, 0};
+    TileWork work[5];
     uint64_t longest = 0;  // bytes of the longest request with tiles
     uint64_t longest_chain = 0;
     bool sorted = true, overlap = false, pred_in = false;
@@ -133,10 +133,9 @@ struct BatchScan {
     uint64_t n_units() const { return n_dec() + n_enc() + n_chain(); }
     uint64_t dec_bytes() const { return bytes[AES_OP_CBC_DEC] + bytes[AES_OP_ECB_DEC]; }
     uint64_t enc_bytes() const { return bytes[AES_OP_CTR] + bytes[AES_OP_ECB_ENC]; }
+    TileWork dec_work() const { return work[AES_OP_CBC_DEC] + work[AES_OP_ECB_DEC]; }
+    TileWork enc_work() const { return work[AES_OP_CTR] + work[AES_OP_ECB_ENC]; }
 };
-
-// Parts of 1 KiB of a request's tiles (tiles are multiples of 1 KiB).
-inline uint64_t kib_parts(uint64_t len) { return (len + 1023) >> 10; }
 
 inline uint64_t tile_count(uint64_t len, uint32_t tile) {
     return len <= tile ? 1 : (len + tile - 1) / tile;  // most requests: no division
@@ -161,13 +160,13 @@ int scan_requests(const aes_req_t *reqs, uint64_t n, uint32_t n_scheds, uint64_t
         last_off = r.offset;
         end = r.offset + r.length;
         b.bytes[r.op] += r.length;
-        b.kib[r.op] += kib_parts(r.length);
         if (r.op == AES_OP_CBC_ENC) {
             b.units[r.op]++;
             longest_chain = std::max(longest_chain, r.length);
             continue;
         }
         longest = std::max(longest, r.length);
+        b.work[r.op].add(r.length);
         const uint64_t t = tile_count(r.length, tile);
         b.units[r.op] += t;
         pred_in |= r.op == AES_OP_CBC_DEC && t > 1;
@@ -230,7 +229,7 @@ struct Planned {
     uint64_t extent = 0;
     uint64_t dec_bytes = 0, ctr_bytes = 0, chain_bytes = 0;
     uint32_t max_tile = 0;  // bytes of the largest tile
-    uint64_t enc_kib = 0;   // parts of 1 KiB of the encryption tiles
+    TileWork dec_work, enc_work;
     bool dec_has_pred_in = false;
     size_t n_ecb = 0;  // ECB-encrypt tiles at the end of ctr
     std::vector<Unit> ecb;       // ECB-encrypt tiles while planning (appended to ctr)
@@ -245,7 +244,7 @@ struct Planned {
         chains.clear();
         payload = extent = 0;
         max_tile = 0;
-        enc_kib = 0;
+        dec_work = enc_work = TileWork();
         dec_bytes = ctr_bytes = chain_bytes = 0;
         dec_has_pred_in = false;
         n_ecb = 0;
@@ -429,8 +428,8 @@ int plan_units(const aes_req_t *reqs, uint64_t n, uint32_t tile_bytes, bool grou
                 p.max_tile = (uint32_t)std::max<uint64_t>(
                     p.max_tile, std::min<uint64_t>(tile_bytes, r.length));
             p.dec_has_pred_in |= r.op == AES_OP_CBC_DEC && t > 1;
-            if (is_enc_tile_op(r.op))
-                p.enc_kib += kib_parts(r.length);
+            if (r.op != AES_OP_CBC_ENC)
+                (is_enc_tile_op(r.op) ? p.enc_work : p.dec_work).add(r.length);
             const size_t at = v.size();
             v.resize(at + t);
             write_request(r.op, r.offset, r.length, r.key_idx, r.iv, tile_bytes, v.data() + at);
@@ -545,7 +544,7 @@ struct PlanView {
     uint64_t chain_bytes;
     uint32_t longest_chain;  // bytes
     uint32_t max_bytes;      // no tile is larger
-    uint64_t enc_kib;  // parts of 1 KiB of the encryption tiles
+    TileWork dec_work, enc_work;
     size_t n_ecb;  // ECB-encrypt tiles: the last n_ecb of the n_ctr encryption tiles
     bool zero_ctrs;  // the counters may not be zero: clear what a launch uses first
 };
@@ -556,7 +555,7 @@ PlanView view_of(const Planned &p, const void *units, void *d_units, uint32_t *d
     return PlanView{units, (Unit *)d_units + (p.dec.size() + p.ctr.size() + p.chains.size()),
                     d_ctrs, p.dec.size(), p.ctr.size(), p.chains.size(), p.dec_has_pred_in,
                     p.dec_bytes, p.ctr_bytes, p.chain_bytes, p.chains.empty() ? 0u : p.chains[0].nbytes,
-                    p.max_tile, p.enc_kib, p.n_ecb, false};
+                    p.max_tile, p.dec_work, p.enc_work, p.n_ecb, false};
 }
 
 }  // namespace
@@ -818,11 +817,11 @@ int launch_planned(const LaunchCtx *ctx, const PlanView &v, const aes_schedule_t
             return hip_fail((hipError_t)e);
         return AES_OK;
     }
-    if ((e = launch_cbcdec_tiles(u_dec, (uint32_t)n_dec, v.max_bytes, d_scheds, n_scheds,
-                                 ctx->d_timg, d_preds, d_in, d_out, v.d_ctrs, v.zero_ctrs,
+    if ((e = launch_cbcdec_tiles(u_dec, (uint32_t)n_dec, v.max_bytes, v.dec_work, d_scheds,
+                                 n_scheds, ctx->d_timg, d_preds, d_in, d_out, v.d_ctrs, v.zero_ctrs,
                                  ctx->tile_dec, ctx->n_cu, stream)))
         return hip_fail((hipError_t)e);
-    if ((e = launch_ctr_tiles(u_ctr, (uint32_t)n_ctr_tab, v.max_bytes, v.enc_kib, d_scheds,
+    if ((e = launch_ctr_tiles(u_ctr, (uint32_t)n_ctr_tab, v.max_bytes, v.enc_work, d_scheds,
                               n_scheds, ctx->d_timg, d_in, d_out, v.d_ctrs + TILE_CTRS,
                               v.zero_ctrs, ctx->tile_ctr, ctx->n_cu, stream)))
         return hip_fail((hipError_t)e);
@@ -920,7 +919,8 @@ PlanView view_of(const BatchScan &b, uint32_t tile) {
     v.chain_bytes = b.bytes[AES_OP_CBC_ENC];
     v.longest_chain = (uint32_t)b.longest_chain;
     v.max_bytes = (uint32_t)std::min<uint64_t>(tile, b.longest);
-    v.enc_kib = b.kib[AES_OP_CTR] + b.kib[AES_OP_ECB_ENC];
+    v.dec_work = b.dec_work();
+    v.enc_work = b.enc_work();
     v.n_ecb = b.units[AES_OP_ECB_ENC];
     return v;
 }
@@ -1110,7 +1110,8 @@ struct ChunkScan {
     int err = AES_OK;
     bool ordered = true;  // nonzero requests in offset order and disjoint
     uint64_t first_off = UINT64_MAX, last_end = 0;
-    uint64_t tiles = 0, payload = 0, longest = 0, kib = 0;
+    uint64_t tiles = 0, payload = 0, longest = 0;
+    TileWork work;
     bool pred_in = false;
 };
 
@@ -1180,14 +1181,15 @@ int single_tiles(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds, uint
             k.last_end = std::max(k.last_end, off + len);
             k.tiles += tile_count(len, tile);
             k.payload += len;
-            k.kib += kib_parts(len);
+            k.work.add(len);
             k.longest = std::max(k.longest, len);
         }
         k.pred_in = op == AES_OP_CBC_DEC && k.longest > tile;
         sc[c] = k;
     });
     // 2. The first error in request order, then disjointness.
-    uint64_t err_at = UINT64_MAX, payload = 0, longest = 0, kib = 0;
+    uint64_t err_at = UINT64_MAX, payload = 0, longest = 0;
+    TileWork work;
     bool ordered = true, pred_in = false;
     uint64_t prev_end = 0;
     base[0] = 0;
@@ -1201,7 +1203,7 @@ int single_tiles(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds, uint
         if (sc[c].first_off != UINT64_MAX)
             prev_end = sc[c].last_end;
         payload += sc[c].payload;
-        kib += sc[c].kib;
+        work = work + sc[c].work;
         longest = std::max(longest, sc[c].longest);
         pred_in |= sc[c].pred_in;
         base[c + 1] = base[c] + sc[c].tiles;
@@ -1237,7 +1239,7 @@ int single_tiles(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds, uint
     v.dec_bytes = dec ? payload : 0;
     v.ctr_bytes = dec ? 0 : payload;
     v.max_bytes = (uint32_t)std::min<uint64_t>(tile, longest);
-    v.enc_kib = dec ? 0 : kib;
+    (dec ? v.dec_work : v.enc_work) = work;
     v.n_ecb = op == AES_OP_ECB_ENC ? n_tiles : 0;
     // 3. Unit records, in request order.
     const auto write = [&](uint64_t lo, uint64_t hi, Unit *u) {

@@ -7,7 +7,6 @@
 #include "aes_chain.h"
 #include "aes_rounds.h"
 #include "internal.h"
-#include "launch_rules.h"
 
 namespace aesgpu {
 

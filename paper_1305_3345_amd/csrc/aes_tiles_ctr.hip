@@ -13,11 +13,11 @@ bool tile_shape_supported(int nb, int wg) {
 }
 
 int launch_ctr_tiles(const Unit *d_units, uint32_t n_units, uint32_t max_bytes,
-                     uint64_t kib_parts, const aes_schedule_t *d_sched, uint32_t n_sched,
+                     const TileWork &work, const aes_schedule_t *d_sched, uint32_t n_sched,
                      const uint32_t *d_timg,
                      const uint8_t *d_in, uint8_t *d_out, uint32_t *d_ctrs, bool zero_ctrs,
                      const TileLaunch &cfg, int n_cu, void *stream) {
-    return launch_tiles<false>(d_units, n_units, max_bytes, kib_parts, d_sched, n_sched, d_timg,
+    return launch_tiles<false>(d_units, n_units, max_bytes, work, d_sched, n_sched, d_timg,
                                nullptr, d_in, d_out, d_ctrs, zero_ctrs, cfg, n_cu, stream);
 }
 

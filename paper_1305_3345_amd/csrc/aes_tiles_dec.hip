@@ -10,11 +10,11 @@
 namespace aesgpu {
 
 int launch_cbcdec_tiles(const Unit *d_units, uint32_t n_units, uint32_t max_bytes,
-                        const aes_schedule_t *d_sched, uint32_t n_sched, const uint32_t *d_timg,
+                        const TileWork &work, const aes_schedule_t *d_sched, uint32_t n_sched, const uint32_t *d_timg,
                         const void *d_preds, const uint8_t *d_in, uint8_t *d_out,
                         uint32_t *d_ctrs, bool zero_ctrs, const TileLaunch &cfg, int n_cu,
                         void *stream) {
-    return launch_tiles<true>(d_units, n_units, max_bytes, UINT64_MAX, d_sched, n_sched, d_timg,
+    return launch_tiles<true>(d_units, n_units, max_bytes, work, d_sched, n_sched, d_timg,
                               d_preds, d_in, d_out, d_ctrs, zero_ctrs, cfg, n_cu, stream);
 }
 

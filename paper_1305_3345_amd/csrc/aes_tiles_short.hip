@@ -6,7 +6,6 @@
 #include <string.h>
 
 #include "internal.h"
-#include "launch_rules.h"
 #include "short_tiles.h"
 
 namespace aesgpu {
@@ -202,11 +201,11 @@ __global__ __launch_bounds__(BD) void k_request_short(
                                : (K)&KERNEL<false, 1, 1024>))
 
 bool launch_tiles_short(bool dec, const Unit *d_units, uint32_t n_units, uint32_t max_bytes,
-                        uint64_t kib_parts, const aes_schedule_t *d_sched, uint32_t n_sched,
+                        const TileWork &work, const aes_schedule_t *d_sched, uint32_t n_sched,
                         const uint32_t *d_timg, const void *d_preds, const uint8_t *d_in,
                         uint8_t *d_out, int n_cu, void *stream, int *err) {
     const TileChoice c =
-        choose_tiles(dec, n_units, max_bytes, kib_parts, aligned16(d_in, d_out), (uint32_t)n_cu);
+        choose_tiles(dec, n_units, max_bytes, work, aligned16(d_in, d_out), (uint32_t)n_cu);
     if (c.kind == TileKind::TILES)
         return false;
     if (c.kind == TileKind::UNEVEN) {

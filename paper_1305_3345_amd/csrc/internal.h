@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "aesgpu.h"
+#include "launch_rules.h"
 
 namespace aesgpu {
 
@@ -78,10 +79,10 @@ struct MixedArgs {
 // Tile launchers take d_ctrs: TILE_CTRS zeroed per-workgroup counters that
 // every launch leaves zeroed (launches sharing them must not overlap); with
 // zero_ctrs they clear the ones they use first.  max_bytes: the largest unit;
-// kib_parts: the units' parts of 1 KiB (encryption side).
+// work: what the units hold.
 constexpr uint32_t TILE_CTRS = 65536;
 int launch_ctr_tiles(const Unit *d_units, uint32_t n_units, uint32_t max_bytes,
-                     uint64_t kib_parts, const aes_schedule_t *d_sched, uint32_t n_sched,
+                     const TileWork &work, const aes_schedule_t *d_sched, uint32_t n_sched,
                      const uint32_t *d_timg,
                      const uint8_t *d_in, uint8_t *d_out, uint32_t *d_ctrs, bool zero_ctrs,
                      const TileLaunch &cfg, int n_cu, void *stream);
@@ -98,7 +99,7 @@ int launch_dec_bitslice(const Unit *d_units, uint32_t n_units, const aes_schedul
 // d_preds: NULL, or one 16-byte predecessor per unit written by
 // launch_snapshot_preds (used for FLAG_PRED_IN units instead of reading d_in).
 int launch_cbcdec_tiles(const Unit *d_units, uint32_t n_units, uint32_t max_bytes,
-                        const aes_schedule_t *d_sched, uint32_t n_sched, const uint32_t *d_timg,
+                        const TileWork &work, const aes_schedule_t *d_sched, uint32_t n_sched, const uint32_t *d_timg,
                         const void *d_preds, const uint8_t *d_in, uint8_t *d_out,
                         uint32_t *d_ctrs, bool zero_ctrs, const TileLaunch &cfg, int n_cu,
                         void *stream);
@@ -119,7 +120,7 @@ int launch_request(const aes_req_t &r, uint32_t tile, const aes_schedule_t *d_sc
 // False: not for them (launch_rules.h), nothing was launched; else *err is the
 // launch's hipError_t.
 bool launch_tiles_short(bool dec, const Unit *d_units, uint32_t n_units, uint32_t max_bytes,
-                        uint64_t kib_parts, const aes_schedule_t *d_sched, uint32_t n_sched,
+                        const TileWork &work, const aes_schedule_t *d_sched, uint32_t n_sched,
                         const uint32_t *d_timg, const void *d_preds, const uint8_t *d_in,
                         uint8_t *d_out, int n_cu, void *stream, int *err);
 // The same for a table in host memory of up to INLINE_UNITS units (none with

@@ -22,19 +22,57 @@ struct TileChoice {
     uint32_t waves = 0, grid = 0;     // waves of a workgroup, workgroups
 };
 
+// What units hold: parts of 1 KiB, and steps of 2 KiB (what a wave of a tile
+// kernel works at once).  Counted by request, so exact for tiles of whole steps.
+struct TileWork {
+    uint64_t kib = 0, steps = 0;
+    void add(uint64_t len) {
+        kib += (len + 1023) >> 10;
+        steps += (len + 2047) >> 11;
+    }
+    TileWork operator+(const TileWork &o) const {
+        TileWork r;
+        r.kib = kib + o.kib;
+        r.steps = steps + o.steps;
+        return r;
+    }
+};
+
 // Where the line lies: microseconds a launch of 4 KiB units, here and with the
 // tile kernels (AES-128 CTR; CBC decryption within 1): 1 to 1,024 units 8 and 9
 // to 15 (the launch call itself takes 7.5), 2,048 11.2 and 16.4, 3,000 14.1 and
 // 16.9, 4,096 18.4 and 17.7, 32,768 114 and 93.  In parts of 2 KiB a compute
 // unit, 4,096 such units are 32.
 constexpr uint32_t SHORT_PARTS_PER_CU = 24;
+// Every unit takes the parts of the largest one there, so units that are nearly
+// all of one step are better off elsewhere once their parts take a second pass:
+// 3,072 units, AES-256 CBC decryption, none, 1%, 6% and 10% of 4 KiB among 64 B
+// 15.7 / 12.2 (tile kernel), 15.7 / 14.4, 15.7 / 15.0, 15.7 / 16.0; AES-128 12.6 /
+// 10.1, 12.6 / 11.7, 12.6 / 12.2, 12.7 / 12.8; CTR 11.6 / 7.0 (uneven units), 11.6
+// / 7.5, 11.6 / 8.2, 11.7 / 8.8.  2,500 units (19.5 parts a compute unit) 14.1 /
+// 12.1, 14.1 / 14.3, 14.2 / 14.7; 2,000 units, one pass, 12.5 / 12.4, 12.6 / 14.2.
+// Decryption units of up to 2 KiB: 4,096 11.2 / 11.0, 4,200 12.3 / 11.2, 5,000 12.8 /
+// 11.8 (CTR stays: 6,144 of them 13.0 / 13.8).  Units of more than 4 KiB wait
+// too long for one wave of a tile kernel.
+constexpr uint32_t ONE_STEP_PER_CU = 16;
+inline bool mostly_one_step(bool dec, uint64_t n_units, uint64_t parts, const TileWork &w,
+                            uint64_t cus) {
+    const uint64_t percent = !dec ? 110 : parts > 20 * cus ? 107 : 101;
+    return 100 * w.steps < percent * n_units;
+}
 // Encryption-side units of uneven sizes, by the parts of 1 KiB that they have
-// (kib_parts, fewer than two a unit, up to this many a compute unit): lengths
+// (fewer than two a unit, up to this many a compute unit): lengths
 // log-uniform to 16 KB, tile kernel against this one, AES-192 CTR 18.1 / 16.0
 // us at 28 parts a compute unit, 23.9 / 20.6 at 42, 29.4 / 23.8 at 55; ECB 14.5
 // / 13.1, 17.7 / 17.1, 23.3 / 20.3.  CBC decryption gained nothing (17.8 / 18.1,
 // 22.3 / 23.3, 29.2 / 27.8), and fuller units lose (4 KiB pages 18.1 / 21.4).
+// Units of mostly one step that left the kernels above: 2,500 and 3,072 of 1,500 B
+// with one of 4 KiB among them 10.3 / 8.4, 10.5 / 9.3.
 constexpr uint32_t UNEVEN_PARTS_PER_CU = 64;
+inline bool uneven_pays(uint64_t n_units, const TileWork &w, bool one_step, uint64_t cus) {
+    return n_units <= 64 * cus && w.kib <= UNEVEN_PARTS_PER_CU * cus &&
+           (w.kib < 2 * n_units || (one_step && w.kib <= 32 * cus));
+}
 
 // Waves per workgroup: as few (4, 8 or 16) as hold the parts on n_wg
 // workgroups at once, and a unit's parts.
@@ -45,10 +83,9 @@ inline uint32_t short_waves(uint64_t parts, uint32_t n_wg, uint32_t unit_parts) 
     return waves;
 }
 
-// n_units units of at most max_bytes each, with kib_parts parts of 1 KiB in all
-// (encryption side), on n_cu compute units.
+// n_units units of at most max_bytes each on n_cu compute units.
 inline TileChoice choose_tiles(bool dec, uint32_t n_units, uint32_t max_bytes,
-                               uint64_t kib_parts, bool aligned, uint32_t n_cu) {
+                               const TileWork &work, bool aligned, uint32_t n_cu) {
     TileChoice c;
     if (!aligned)
         return c;
@@ -67,9 +104,11 @@ inline TileChoice choose_tiles(bool dec, uint32_t n_units, uint32_t max_bytes,
             break;
     }
     const uint64_t parts = (uint64_t)n_units << lg;
-    if (lg > 4 || (parts > SHORT_PARTS_PER_CU * cus && max_bytes > 1024)) {
-        if (dec || n_units > 64ull * cus || kib_parts >= 2ull * n_units ||
-            kib_parts > UNEVEN_PARTS_PER_CU * (uint64_t)cus)
+    const bool one_step = parts > (uint64_t)ONE_STEP_PER_CU * cus && nb == 2 && lg <= 1 &&
+                          (dec || lg == 1) &&
+                          mostly_one_step(dec, n_units, parts, work, cus);
+    if (lg > 4 || one_step || (parts > SHORT_PARTS_PER_CU * cus && max_bytes > 1024)) {
+        if (dec || !uneven_pays(n_units, work, one_step, cus))
             return c;
         c.kind = TileKind::UNEVEN;
         c.waves = 16;

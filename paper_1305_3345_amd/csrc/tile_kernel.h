@@ -108,7 +108,7 @@ inline TileKernel pick_tile_kernel(int nb, int wg) {
 // with zero_ctrs, any.
 template <bool DEC>
 inline int launch_tiles(const Unit *d_units, uint32_t n_units, uint32_t max_bytes,
-                        uint64_t kib_parts, const aes_schedule_t *d_sched, uint32_t n_sched,
+                        const TileWork &work, const aes_schedule_t *d_sched, uint32_t n_sched,
                         const uint32_t *d_timg, const void *d_preds, const uint8_t *d_in,
                         uint8_t *d_out, uint32_t *d_ctrs, bool zero_ctrs, const TileLaunch &cfg,
                         int n_cu, void *stream) {
@@ -118,7 +118,7 @@ inline int launch_tiles(const Unit *d_units, uint32_t n_units, uint32_t max_byte
     // them; a shape or grid that was set is kept.
     int err;
     if (is_default(cfg) &&
-        launch_tiles_short(DEC, d_units, n_units, max_bytes, kib_parts, d_sched, n_sched, d_timg,
+        launch_tiles_short(DEC, d_units, n_units, max_bytes, work, d_sched, n_sched, d_timg,
                            d_preds, d_in, d_out, n_cu, stream, &err))
         return err;
     const TileKernel k = pick_tile_kernel<DEC>(cfg.nb, cfg.wg_threads);

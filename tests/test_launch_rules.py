@@ -13,9 +13,15 @@ using namespace aesgpu;
 extern "C" int aligned(uint64_t in, uint64_t out) {
     return aligned16((const void *)in, (const void *)out);
 }
-extern "C" void choose(int dec, uint32_t n, uint32_t max_bytes, uint64_t kib, int ok,
-                       uint32_t n_cu, uint32_t *out) {
-    const TileChoice c = choose_tiles(dec, n, max_bytes, kib, ok, n_cu);
+extern "C" void choose(int dec, uint32_t n, const uint32_t *lengths, int ok, uint32_t n_cu,
+                       uint32_t *out) {
+    TileWork w;
+    uint32_t max_bytes = 0;
+    for (uint32_t i = 0; i < n; i++) {
+        w.add(lengths[i]);
+        max_bytes = lengths[i] > max_bytes ? lengths[i] : max_bytes;
+    }
+    const TileChoice c = choose_tiles(dec, n, max_bytes, w, ok, n_cu);
     out[0] = (uint32_t)c.kind;
     out[1] = c.nb;
     out[2] = c.parts_log2;
@@ -48,8 +54,8 @@ def rules(tmp_path_factory):
 def choose(rules, lengths, dec=False, ok=True, cus=CUS):
     """(kind, blocks per lane, log2 parts, waves, workgroups) for units of these bytes."""
     out = (ctypes.c_uint32 * 5)()
-    kib = 2**64 - 1 if dec else sum((v + 1023) // 1024 for v in lengths)
-    rules.choose(int(dec), len(lengths), max(lengths), ctypes.c_uint64(kib), int(ok), cus, out)
+    n = len(lengths)
+    rules.choose(int(dec), n, (ctypes.c_uint32 * n)(*lengths), int(ok), cus, out)
     return tuple(out)
 
 
@@ -90,3 +96,21 @@ def test_chains_alone(rules, n, longest, mean, lanes):
     """What was measured faster on 256 compute units of sixteen waves."""
     assert rules.lanes(n, longest, ctypes.c_uint64(n * mean), 1, 16 * CUS) == lanes
     assert rules.lanes(n, longest, ctypes.c_uint64(n * mean), 0, 16 * CUS) == 1
+
+
+@pytest.mark.parametrize("lengths,dec,ctr", [
+    # Nearly all of one step, parts beyond one pass: not padded to 4 KiB each.
+    ([64] * 3071 + [4096], TILES, UNEVEN), ([1008] * 2499 + [4096], TILES, UNEVEN),
+    ([1500] * 3071 + [4096], TILES, UNEVEN), ([64] * 2900 + [4096] * 172, TILES, UNEVEN),
+    ([64] * 2480 + [4096] * 20, TILES, UNEVEN), ([64] * 2420 + [4096] * 80, SHORT, UNEVEN),
+    # One pass, or enough units of two steps.
+    ([64] * 2047 + [4096], SHORT, SHORT), ([64] * 2700 + [4096] * 372, SHORT, SHORT),
+    ([4096] * 3072, SHORT, SHORT), ([4096] * 3073, TILES, TILES),
+    # One step each.
+    ([2048] * 4096, SHORT, SHORT), ([2048] * 4097, TILES, SHORT), ([1040] * 6144, TILES, SHORT),
+    ([1024] * 60000, SHORT, SHORT),
+    # More than two steps take a tile kernel's single wave too long.
+    ([64] * 1500 + [8192], SHORT, SHORT), ([64] * 767 + [16384], SHORT, SHORT)])
+def test_short_launches_by_what_units_hold(rules, lengths, dec, ctr):
+    assert choose(rules, lengths, dec=True)[0] == dec
+    assert choose(rules, lengths)[0] == ctr
