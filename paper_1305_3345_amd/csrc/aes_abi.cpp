@@ -120,21 +120,21 @@ bool is_enc_tile_op(uint32_t op) { return op == AES_OP_CTR || op == AES_OP_ECB_E
 
 // What one pass over a request list finds: tiles (for CBC encryption: chains)
 // and bytes by operation, and whether the nonempty requests come in offset
-// order without overlapping.
+// order without overlapping (if not, check_disjoint decides).
 struct BatchScan {
     uint64_t units[5] = {0, 0, 0, 0, 0}, bytes[5] = {0, 0, 0, 0, 0};
-    TileWork work[5];
+    uint64_t work[5] = {0, 0, 0, 0, 0};  // sums of TileWork::of
     uint64_t longest = 0;  // bytes of the longest request with tiles
     uint64_t longest_chain = 0;
-    bool sorted = true, overlap = false, pred_in = false;
+    bool ordered = true, pred_in = false;
     uint64_t n_dec() const { return units[AES_OP_CBC_DEC] + units[AES_OP_ECB_DEC]; }
     uint64_t n_enc() const { return units[AES_OP_CTR] + units[AES_OP_ECB_ENC]; }
     uint64_t n_chain() const { return units[AES_OP_CBC_ENC]; }
     uint64_t n_units() const { return n_dec() + n_enc() + n_chain(); }
     uint64_t dec_bytes() const { return bytes[AES_OP_CBC_DEC] + bytes[AES_OP_ECB_DEC]; }
     uint64_t enc_bytes() const { return bytes[AES_OP_CTR] + bytes[AES_OP_ECB_ENC]; }
-    TileWork dec_work() const { return work[AES_OP_CBC_DEC] + work[AES_OP_ECB_DEC]; }
-    TileWork enc_work() const { return work[AES_OP_CTR] + work[AES_OP_ECB_ENC]; }
+    TileWork dec_work() const { return {work[AES_OP_CBC_DEC] + work[AES_OP_ECB_DEC]}; }
+    TileWork enc_work() const { return {work[AES_OP_CTR] + work[AES_OP_ECB_ENC]}; }
 };
 
 inline uint64_t tile_count(uint64_t len, uint32_t tile) {
@@ -144,8 +144,8 @@ inline uint64_t tile_count(uint64_t len, uint32_t tile) {
 // The per-request rules of validate, in its order of errors.
 int scan_requests(const aes_req_t *reqs, uint64_t n, uint32_t n_scheds, uint64_t buf_bytes,
                   uint32_t tile, BatchScan &b) {
-    uint64_t last_off = 0, end = 0, longest = 0, longest_chain = 0;
-    bool sorted = true, overlap = false, pred_in = false;
+    uint64_t end = 0, longest = 0, longest_chain = 0;
+    bool ordered = true, pred_in = false;
     for (uint64_t i = 0; i < n; i++) {
         const aes_req_t &r = reqs[i];
         if (r.op > AES_OP_ECB_DEC)
@@ -155,31 +155,28 @@ int scan_requests(const aes_req_t *reqs, uint64_t n, uint32_t n_scheds, uint64_t
             return st;
         if (!r.length)
             continue;
-        sorted &= r.offset >= last_off;
-        overlap |= r.offset < end;
-        last_off = r.offset;
+        ordered &= r.offset >= end;
         end = r.offset + r.length;
         b.bytes[r.op] += r.length;
+        b.work[r.op] += TileWork::of(r.length);
         if (r.op == AES_OP_CBC_ENC) {
             b.units[r.op]++;
             longest_chain = std::max(longest_chain, r.length);
             continue;
         }
         longest = std::max(longest, r.length);
-        b.work[r.op].add(r.length);
         const uint64_t t = tile_count(r.length, tile);
         b.units[r.op] += t;
         pred_in |= r.op == AES_OP_CBC_DEC && t > 1;
     }
     b.longest = longest;
     b.longest_chain = longest_chain;
-    b.sorted = sorted;
-    b.overlap = overlap;
+    b.ordered = ordered;
     b.pred_in = pred_in;
     return AES_OK;
 }
 
-// The disjointness rule for a list that is not in offset order; ranges has
+// The disjointness rule for a list that is not in order; ranges has
 // room for every nonempty request.
 int check_disjoint(const aes_req_t *reqs, uint64_t n, std::pair<uint64_t, uint64_t> *ranges) {
     uint64_t k = 0;
@@ -429,7 +426,7 @@ int plan_units(const aes_req_t *reqs, uint64_t n, uint32_t tile_bytes, bool grou
                     p.max_tile, std::min<uint64_t>(tile_bytes, r.length));
             p.dec_has_pred_in |= r.op == AES_OP_CBC_DEC && t > 1;
             if (r.op != AES_OP_CBC_ENC)
-                (is_enc_tile_op(r.op) ? p.enc_work : p.dec_work).add(r.length);
+                (is_enc_tile_op(r.op) ? p.enc_work : p.dec_work).sum += TileWork::of(r.length);
             const size_t at = v.size();
             v.resize(at + t);
             write_request(r.op, r.offset, r.length, r.key_idx, r.iv, tile_bytes, v.data() + at);
@@ -939,7 +936,7 @@ int run_batch(aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_scheds,
     BatchScan b;
     if ((st = scan_requests(reqs, n, n_scheds, buf_bytes, tile, b)))
         return st;
-    if (!b.sorted) {
+    if (!b.ordered) {
         std::vector<std::pair<uint64_t, uint64_t>> ranges;
         try {
             ranges.resize(n);
@@ -948,8 +945,6 @@ int run_batch(aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_scheds,
         }
         if ((st = check_disjoint(reqs, n, ranges.data())))
             return st;
-    } else if (b.overlap) {
-        return AES_ERR_OVERLAP;
     }
     PlanView v = view_of(b, tile);
     if (v.n_dec >= (1ull << 32) || v.n_ctr >= (1ull << 32) || v.n_chain >= (1ull << 32))
@@ -1054,12 +1049,8 @@ int run_batch_noalloc(aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_s
     std::lock_guard<std::mutex> lk(g_noalloc_mu);
     // 2. Disjoint output ranges (as many as there are nonempty requests, at
     //    most n_units, where they have to be sorted).
-    if (!b.sorted) {
-        if ((st = check_disjoint(reqs, n, g_noalloc_ranges)))
-            return st;
-    } else if (b.overlap) {
-        return AES_ERR_OVERLAP;
-    }
+    if (!b.ordered && (st = check_disjoint(reqs, n, g_noalloc_ranges)))
+        return st;
     if (!n_units)
         return AES_OK;
     if (ctx->device == AES_DEVICE_NONE)
@@ -1110,8 +1101,7 @@ struct ChunkScan {
     int err = AES_OK;
     bool ordered = true;  // nonzero requests in offset order and disjoint
     uint64_t first_off = UINT64_MAX, last_end = 0;
-    uint64_t tiles = 0, payload = 0, longest = 0;
-    TileWork work;
+    uint64_t tiles = 0, payload = 0, longest = 0, work = 0;
     bool pred_in = false;
 };
 
@@ -1174,22 +1164,19 @@ int single_tiles(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds, uint
             }
             if (!len)
                 continue;
-            if (off < k.last_end || (k.first_off != UINT64_MAX && off < k.first_off))
-                k.ordered = false;
-            if (k.first_off == UINT64_MAX)
-                k.first_off = off;
+            k.ordered &= off >= k.last_end;
+            k.first_off = std::min(k.first_off, off);
             k.last_end = std::max(k.last_end, off + len);
             k.tiles += tile_count(len, tile);
             k.payload += len;
-            k.work.add(len);
+            k.work += TileWork::of(len);
             k.longest = std::max(k.longest, len);
         }
         k.pred_in = op == AES_OP_CBC_DEC && k.longest > tile;
         sc[c] = k;
     });
     // 2. The first error in request order, then disjointness.
-    uint64_t err_at = UINT64_MAX, payload = 0, longest = 0;
-    TileWork work;
+    uint64_t err_at = UINT64_MAX, payload = 0, longest = 0, work = 0;
     bool ordered = true, pred_in = false;
     uint64_t prev_end = 0;
     base[0] = 0;
@@ -1203,7 +1190,7 @@ int single_tiles(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds, uint
         if (sc[c].first_off != UINT64_MAX)
             prev_end = sc[c].last_end;
         payload += sc[c].payload;
-        work = work + sc[c].work;
+        work += sc[c].work;
         longest = std::max(longest, sc[c].longest);
         pred_in |= sc[c].pred_in;
         base[c + 1] = base[c] + sc[c].tiles;
@@ -1239,7 +1226,7 @@ int single_tiles(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds, uint
     v.dec_bytes = dec ? payload : 0;
     v.ctr_bytes = dec ? 0 : payload;
     v.max_bytes = (uint32_t)std::min<uint64_t>(tile, longest);
-    (dec ? v.dec_work : v.enc_work) = work;
+    (dec ? v.dec_work : v.enc_work).sum = work;
     v.n_ecb = op == AES_OP_ECB_ENC ? n_tiles : 0;
     // 3. Unit records, in request order.
     const auto write = [&](uint64_t lo, uint64_t hi, Unit *u) {

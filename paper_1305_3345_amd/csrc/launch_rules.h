@@ -24,18 +24,15 @@ struct TileChoice {
 
 // What units hold: parts of 1 KiB, and steps of 2 KiB (what a wave of a tile
 // kernel works at once).  Counted by request, so exact for tiles of whole steps.
+// (Both in one word, one addition a request: they are of disjoint ranges of a
+// buffer in device memory, far below 2^32 KiB.)
 struct TileWork {
-    uint64_t kib = 0, steps = 0;
-    void add(uint64_t len) {
-        kib += (len + 1023) >> 10;
-        steps += (len + 2047) >> 11;
+    uint64_t sum = 0;  // parts, steps << 32
+    static uint64_t of(uint64_t len) {
+        return ((len + 1023) >> 10) + ((len + 2047) >> 11 << 32);
     }
-    TileWork operator+(const TileWork &o) const {
-        TileWork r;
-        r.kib = kib + o.kib;
-        r.steps = steps + o.steps;
-        return r;
-    }
+    uint64_t kib() const { return (uint32_t)sum; }
+    uint64_t steps() const { return sum >> 32; }
 };
 
 // Where the line lies: microseconds a launch of 4 KiB units, here and with the
@@ -58,7 +55,7 @@ constexpr uint32_t ONE_STEP_PER_CU = 16;
 inline bool mostly_one_step(bool dec, uint64_t n_units, uint64_t parts, const TileWork &w,
                             uint64_t cus) {
     const uint64_t percent = !dec ? 110 : parts > 20 * cus ? 107 : 101;
-    return 100 * w.steps < percent * n_units;
+    return 100 * w.steps() < percent * n_units;
 }
 // Encryption-side units of uneven sizes, by the parts of 1 KiB that they have
 // (fewer than two a unit, up to this many a compute unit): lengths
@@ -70,8 +67,8 @@ inline bool mostly_one_step(bool dec, uint64_t n_units, uint64_t parts, const Ti
 // with one of 4 KiB among them 10.3 / 8.4, 10.5 / 9.3.
 constexpr uint32_t UNEVEN_PARTS_PER_CU = 64;
 inline bool uneven_pays(uint64_t n_units, const TileWork &w, bool one_step, uint64_t cus) {
-    return n_units <= 64 * cus && w.kib <= UNEVEN_PARTS_PER_CU * cus &&
-           (w.kib < 2 * n_units || (one_step && w.kib <= 32 * cus));
+    return n_units <= 64 * cus && w.kib() <= UNEVEN_PARTS_PER_CU * cus &&
+           (w.kib() < 2 * n_units || (one_step && w.kib() <= 32 * cus));
 }
 
 // Waves per workgroup: as few (4, 8 or 16) as hold the parts on n_wg

@@ -18,7 +18,7 @@ extern "C" void choose(int dec, uint32_t n, const uint32_t *lengths, int ok, uin
     TileWork w;
     uint32_t max_bytes = 0;
     for (uint32_t i = 0; i < n; i++) {
-        w.add(lengths[i]);
+        w.sum += TileWork::of(lengths[i]);
         max_bytes = lengths[i] > max_bytes ? lengths[i] : max_bytes;
     }
     const TileChoice c = choose_tiles(dec, n, max_bytes, w, ok, n_cu);
