@@ -1105,6 +1105,17 @@ struct ChunkScan {
     bool pred_in = false;
 };
 
+// The unit records of requests [lo, hi) of a single-op call, from u on.  (Plain
+// arguments: in a closure, every store to a record would have them read again.)
+void write_single(uint32_t op, const uint64_t *offsets, const uint64_t *lengths,
+                  const uint32_t *key_idx, const uint8_t *ivs, uint32_t tile, uint64_t lo,
+                  uint64_t hi, Unit *u) {
+    for (uint64_t i = lo; i < hi; i++)
+        if (lengths[i])
+            u = write_request(op, offsets[i], lengths[i], key_idx[i],
+                              ivs ? ivs + 16 * i : nullptr, tile, u);
+}
+
 // A single-op call over tiles (CBC decryption, CTR, ECB): the requests are
 // checked in chunks (on the context's threads if there are many; the rules and
 // error precedence of validate), then each chunk writes its unit records
@@ -1229,22 +1240,17 @@ int single_tiles(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds, uint
     (dec ? v.dec_work : v.enc_work).sum = work;
     v.n_ecb = op == AES_OP_ECB_ENC ? n_tiles : 0;
     // 3. Unit records, in request order.
-    const auto write = [&](uint64_t lo, uint64_t hi, Unit *u) {
-        for (uint64_t i = lo; i < hi; i++)
-            if (lengths[i])
-                u = write_request(op, offsets[i], lengths[i], key_idx[i],
-                                  ivs ? ivs + 16 * i : nullptr, tile, u);
-    };
     if (n_tiles <= INLINE_UNITS) {
         Unit few[INLINE_UNITS];
-        write(0, n, few);
+        write_single(op, offsets, lengths, key_idx, ivs, tile, 0, n, few);
         if (launch_few(ctx, few, v, d_scheds, n_scheds, d_in, d_out, stream, &st))
             return st;
     }
     const auto put = [&](Unit *out) {
         run([&](int c) {
             const uint64_t lo = (uint64_t)c * PAR_CHUNK;
-            write(lo, std::min(n, lo + PAR_CHUNK), out + base[c]);
+            write_single(op, offsets, lengths, key_idx, ivs, tile, lo, std::min(n, lo + PAR_CHUNK),
+                         out + base[c]);
         });
     };
     return launch_table(ctx, v, put, d_scheds, n_scheds, d_in, d_out, stream);
