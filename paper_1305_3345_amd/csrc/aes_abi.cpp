@@ -895,6 +895,7 @@ int launch_table(aes_ctx *ctx, PlanView v, const Write &write, const aes_schedul
     write((Unit *)s->h_stage);
     if ((st = upload_units(ctx, *s, n * sizeof(Unit), stream, &v.d_units)))
         return st;
+    v.enc_work.host_table = v.d_units == s->d_stage;
     v.d_preds = (Unit *)s->d_units + n;
     v.d_ctrs = s->d_ctrs;
     if ((st = launch_planned(ctx, v, d_scheds, n_scheds, d_in, d_out, stream)))

@@ -79,22 +79,29 @@ __device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t v) {
     return v;
 }
 
-// Encryption-side units of any sizes: every workgroup takes the next `per`
-// units, the first `more` workgroups one more (at most 64), and its waves take
-// their 1 KiB parts in turn, empty ones left out.  The first wave fetches the
-// records for all, through LDS; each wave then holds record `lane` and finds a
-// part's unit with a ballot over the running sum of the parts.
+// Encryption-side units of any sizes: every workgroup takes up to 64 units, and
+// its waves take their 1 KiB parts in turn, empty ones left out.  The first wave
+// fetches the records for all, through LDS; each wave then holds record `lane`
+// and finds a part's unit with a ballot over the running sum of the parts.
+// Units of a table in device memory are dealt out one by one (uneven_unit), so
+// that a list in order of size loads all workgroups alike: 4,289 requests
+// log-uniform to 16 KB in ascending order, AES-128 CTR, 14.4 us against 23.1 in
+// runs of consecutive units, shuffled 16.6 against 18.4.  A table that is read
+// over the host link (inv_wg 0) is taken in runs, whose records come together:
+// 3,001 shuffled requests 21.8 us against 29.3, ascending 25.0 against 27.4.
 __global__ __launch_bounds__(1024) void k_tiles_uneven(
-    const Unit *__restrict__ units, uint32_t per, uint32_t more,
-    const uint32_t *__restrict__ timg, const aes_schedule_t *__restrict__ sched, const uint8_t *in,
+    const Unit *__restrict__ units, uint32_t n_units, uint32_t per, uint32_t more,
+    uint32_t n_wg, uint32_t inv_wg, const uint32_t *__restrict__ timg, const aes_schedule_t *__restrict__ sched, const uint8_t *in,
     uint32_t n_sched, uint8_t *out) {
     __shared__ __align__(16) uint32_t lds[LDS_ENC_WORDS + 512u];
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t lo = blockIdx.x * per + (blockIdx.x < more ? blockIdx.x : more);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t g = blockIdx.x;
+    const uint32_t u = inv_wg ? uneven_unit(g, lane, n_wg, inv_wg)
+                              : g * per + (g < more ? g : more) + lane;
     uint4 a = make_uint4(0u, 0u, 0u, 0u), b = a;
-    if (wave == 0u && lane < per + (blockIdx.x < more)) {
-        const uint4 *p = reinterpret_cast<const uint4 *>(units + lo + lane);
+    if (wave == 0u && u < n_units && lane < per + (inv_wg ? more != 0u : g < more)) {
+        const uint4 *p = reinterpret_cast<const uint4 *>(units + u);
         a = p[0];
         b = p[1];
     }
@@ -210,8 +217,9 @@ bool launch_tiles_short(bool dec, const Unit *d_units, uint32_t n_units, uint32_
         return false;
     if (c.kind == TileKind::UNEVEN) {
         hipLaunchKernelGGL(k_tiles_uneven, dim3(c.grid), dim3(64 * c.waves), 0,
-                           (hipStream_t)stream, d_units, n_units / c.grid, n_units % c.grid, d_timg,
-                           d_sched, d_in, n_sched, d_out);
+                           (hipStream_t)stream, d_units, n_units, n_units / c.grid, n_units % c.grid,
+                           c.grid, work.host_table ? 0u : uneven_inverse(c.grid), d_timg, d_sched,
+                           d_in, n_sched, d_out);
         *err = hipGetLastError();
         return true;
     }

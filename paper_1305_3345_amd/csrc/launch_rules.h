@@ -27,7 +27,8 @@ struct TileChoice {
 // (Both in one word, one addition a request: they are of disjoint ranges of a
 // buffer in device memory, far below 2^32 KiB.)
 struct TileWork {
-    uint64_t sum = 0;  // parts, steps << 32
+    uint64_t sum = 0;         // parts, steps << 32
+    bool host_table = false;  // the unit table is read over the host link
     static uint64_t of(uint64_t len) {
         return ((len + 1023) >> 10) + ((len + 2047) >> 11 << 32);
     }
@@ -69,6 +70,17 @@ constexpr uint32_t UNEVEN_PARTS_PER_CU = 64;
 inline bool uneven_pays(uint64_t n_units, const TileWork &w, bool one_step, uint64_t cus) {
     return n_units <= 64 * cus && w.kib() <= UNEVEN_PARTS_PER_CU * cus &&
            (w.kib() < 2 * n_units || (one_step && w.kib() <= 32 * cus));
+}
+
+// The unit that workgroup wg of n_wg (at most 65,535; inv its uneven_inverse)
+// takes with lane `lane`.  Round k deals units k n_wg .. k n_wg + n_wg - 1, lane k
+// of workgroup wg the one at place (wg + 37 k) mod n_wg.
+// (constexpr: the kernel calls it too.)
+inline uint32_t uneven_inverse(uint32_t n_wg) { return 0xFFFFFFFFu / n_wg; }
+constexpr uint32_t uneven_unit(uint32_t wg, uint32_t lane, uint32_t n_wg, uint32_t inv) {
+    const uint32_t at = wg + 37u * lane;  // below 2^17
+    const uint32_t r = at - (uint32_t)((uint64_t)at * inv >> 32) * n_wg;  // below 2 n_wg
+    return lane * n_wg + (r >= n_wg ? r - n_wg : r);
 }
 
 // Waves per workgroup: as few (4, 8 or 16) as hold the parts on n_wg

@@ -4,6 +4,7 @@ import ctypes
 import os
 import subprocess
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -27,6 +28,12 @@ extern "C" void choose(int dec, uint32_t n, const uint32_t *lengths, int ok, uin
     out[2] = c.parts_log2;
     out[3] = c.waves;
     out[4] = c.grid;
+}
+extern "C" void uneven(uint32_t n_wg, uint32_t *out) {  // [n_wg][64]
+    const uint32_t inv = uneven_inverse(n_wg);
+    for (uint32_t g = 0; g < n_wg; g++)
+        for (uint32_t lane = 0; lane < 64; lane++)
+            out[64 * g + lane] = uneven_unit(g, lane, n_wg, inv);
 }
 extern "C" int mixed_lanes(uint32_t n, uint32_t longest, int grouped, uint32_t n_wg,
                            uint64_t tile_bytes) {
@@ -114,3 +121,43 @@ def test_chains_alone(rules, n, longest, mean, lanes):
 def test_short_launches_by_what_units_hold(rules, lengths, dec, ctr):
     assert choose(rules, lengths, dec=True)[0] == dec
     assert choose(rules, lengths)[0] == ctr
+
+
+def dealt(rules, n_wg):
+    out = np.zeros((n_wg, 64), np.uint32)
+    rules.uneven(n_wg, out.ctypes.data_as(ctypes.c_void_p))
+    return out
+
+
+@pytest.mark.parametrize("n_wg", [1, 2, 3, 36, 37, 38, 74, 255, 256, 257, 304, 4096, 65535])
+def test_uneven_units_are_dealt_once(rules, n_wg):
+    """Every unit below 64 per workgroup goes to one lane of one workgroup, the
+    first n units to the first lanes."""
+    out = dealt(rules, n_wg)
+    assert np.array_equal(np.sort(out.ravel()), np.arange(64 * n_wg))
+    assert (out // n_wg == np.arange(64)).all()
+
+
+@pytest.mark.parametrize("order", ["ascending", "descending", "blocks", "period"])
+def test_uneven_units_in_order_of_size(rules, order):
+    """The largest workgroup's parts stay near the mean for sorted lists, lists
+    of blocks of one size, and flows that repeat every 512 requests (the ranges
+    of consecutive units that the kernel took before hold 1.7 to 2.1 times the
+    mean where a list is sorted)."""
+    n = 6000
+    rng = np.random.default_rng(1)
+    lengths = np.exp(rng.uniform(0, np.log(4097), n)).astype(np.uint64)
+    lengths = np.sort(lengths)
+    if order == "descending":
+        lengths = lengths[::-1]
+    elif order == "blocks":
+        lengths = lengths.reshape(10, -1)[rng.permutation(10)].ravel()
+    elif order == "period":
+        lengths = lengths[rng.integers(0, n, 512)][np.arange(n) % 512]
+    parts = np.zeros(64 * CUS, np.int64)
+    parts[:n] = (lengths + 1023) // 1024
+    load = parts[dealt(rules, CUS)].sum(axis=1)
+    # Sorted: a unit a round, and a round's units differ by one part at most.
+    # Random flows: 23 or 24 units a workgroup, four standard deviations.
+    limit = 1.25 if order != "period" else 1 + 4 * parts[:n].std() / parts[:n].mean() / 23 ** .5
+    assert load.max() <= limit * load.mean(), (load.max(), load.mean())
