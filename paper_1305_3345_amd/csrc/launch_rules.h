@@ -66,10 +66,22 @@ inline bool mostly_one_step(bool dec, uint64_t n_units, uint64_t parts, const Ti
 // 22.3 / 23.3, 29.2 / 27.8), and fuller units lose (4 KiB pages 18.1 / 21.4).
 // Units of mostly one step that left the kernels above: 2,500 and 3,072 of 1,500 B
 // with one of 4 KiB among them 10.3 / 8.4, 10.5 / 9.3.
+// Units that nearly fill one step each are what the tile kernel is best at: a
+// step of such a unit costs it about 18, a step of a longer unit 25, a part here
+// 13, or 11 while there are few (in these units, fitted to what follows).  Of
+// units of 1 and 2 KiB, 30%, 50%, 70% and 90% of them the latter, AES-128 CTR, at
+// 40 parts a compute unit 17.5 / 15.7, 15.7 / 14.9, 13.7 / 14.3, 13.3 / 13.4; at 56
+// 19.6 / 18.8, 17.6 / 18.7, 16.8 / 18.2, 16.8 / 17.3; at 63 22.7 / 19.9, 19.2 / 19.9,
+// 17.6 / 19.9, 17.2 / 19.7; AES-256 ECB at 56 26.0 / 23.2, 24.5 / 23.2, 22.4 / 22.6,
+// 21.6 / 21.2; CTR, 60%, at 52 17.4 / 18.2.
 constexpr uint32_t UNEVEN_PARTS_PER_CU = 64;
 inline bool uneven_pays(uint64_t n_units, const TileWork &w, bool one_step, uint64_t cus) {
-    return n_units <= 64 * cus && w.kib() <= UNEVEN_PARTS_PER_CU * cus &&
-           (w.kib() < 2 * n_units || (one_step && w.kib() <= 32 * cus));
+    if (n_units > 64 * cus || w.kib() > UNEVEN_PARTS_PER_CU * cus)
+        return false;
+    if (w.kib() <= 32 * cus)  // two passes
+        return one_step || w.kib() < 2 * n_units;
+    const uint64_t part = w.kib() <= 48 * cus ? 11 : 13;
+    return w.kib() < 2 * n_units && part * w.kib() + 14 * n_units < 32 * w.steps();
 }
 
 // The unit that workgroup wg of n_wg (at most 65,535; inv its uneven_inverse)

@@ -161,3 +161,30 @@ def test_uneven_units_in_order_of_size(rules, order):
     # Random flows: 23 or 24 units a workgroup, four standard deviations.
     limit = 1.25 if order != "period" else 1 + 4 * parts[:n].std() / parts[:n].mean() / 23 ** .5
     assert load.max() <= limit * load.mean(), (load.max(), load.mean())
+
+
+@pytest.mark.parametrize("per_cu,share,kind", [
+    (40, .3, UNEVEN), (40, .5, UNEVEN), (40, .7, TILES), (40, .9, TILES), (47, .6, UNEVEN), (52, .6, TILES),
+    (56, .3, UNEVEN), (56, .5, TILES), (63, .3, UNEVEN), (63, .5, TILES), (63, .9, TILES)])
+def test_uneven_units_that_fill_a_step(rules, per_cu, share, kind):
+    """Units of 1 KiB and, by `share`, 2 KiB: the tile kernel's step."""
+    n = int(per_cu * CUS / (1 + share))
+    big = int(share * n)
+    assert choose(rules, [2048] * big + [1024] * (n - big - 1) + [2500])[0] == kind
+
+
+@pytest.mark.parametrize("per_cu", [40, 52, 63])
+@pytest.mark.parametrize("lo,hi", [(1, 16001), (1, 3000)])
+def test_uneven_units_of_any_size(rules, per_cu, lo, hi):
+    """Log-uniform to 16 KB in tiles of 4 KiB, uniform to 3,000 B."""
+    rng = np.random.default_rng(3)
+    draw = rng.uniform(np.log(lo), np.log(hi), 20000) if hi > 4096 else rng.uniform(lo, hi, 20000)
+    lengths = np.exp(draw) if hi > 4096 else draw
+    units, parts = [], 0
+    for v in lengths.astype(int):
+        tiles = [4096] * (v // 4096) + ([v % 4096] if v % 4096 else [])
+        units += tiles
+        parts += sum((t + 1023) // 1024 for t in tiles)
+        if parts >= per_cu * CUS:
+            break
+    assert choose(rules, units)[0] == UNEVEN
