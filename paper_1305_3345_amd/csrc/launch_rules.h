@@ -111,7 +111,7 @@ inline TileChoice choose_tiles(bool dec, uint32_t n_units, uint32_t max_bytes,
     if (!aligned)
         return c;
     const uint32_t cus = n_cu < 65535u ? n_cu : 65535u;
-    // One block per lane for one pass, else two.  Units of up to 1 KiB, which
+    // One block per lane for one pass (of units up to 16 KiB), else two.  Units of up to 1 KiB, which
     // fill at most half of a tile kernel's step, run here in any number, one
     // block per lane: 16,384 units of 256 B 17.4 us (AES-128 CTR) against 23.3
     // there, 65,536 units of 1 KiB 59.3 against 82.8, of 1 to 1,024 B 63.7
@@ -121,7 +121,8 @@ inline TileChoice choose_tiles(bool dec, uint32_t n_units, uint32_t max_bytes,
         lg = 0;
         while (lg < 5 && (uint64_t)max_bytes > ((1024ull * nb) << lg))
             lg++;
-        if (nb == 2 || ((uint64_t)n_units << lg) <= 16ull * cus || max_bytes <= 1024)
+        if (nb == 2 || max_bytes <= 1024 ||
+            (lg <= 4 && ((uint64_t)n_units << lg) <= 16ull * cus))
             break;
     }
     const uint64_t parts = (uint64_t)n_units << lg;

@@ -39,3 +39,17 @@ def test_mostly_one_step(ctx, op, n, small, big, n_big, inplace):
     lengths = np.full(n, small)
     lengths[np.random.default_rng(n).permutation(n)[:n_big]] = big
     check(ctx, op, lengths, inplace)
+
+
+@pytest.mark.parametrize("inplace", [False, True])
+@pytest.mark.parametrize("op", list(OPS))
+@pytest.mark.parametrize("n", [1, 8, 128, 129])
+def test_few_large_units(ctx, op, n, inplace):
+    """Tiles of 32 KiB: units over 16 KiB, some in requests of two tiles."""
+    print(f"[gpu] {op}: {n} units to 32 KiB, inplace={inplace}", flush=True)
+    cfg = ctx.get_config()
+    ctx.set_config(tile_bytes=32768)
+    lengths = np.random.default_rng(n).integers(16385, 32769, n)
+    lengths[0] = 65536 - 48 if n > 1 else 32768
+    check(ctx, op, lengths, inplace)
+    ctx.set_config(**cfg)

@@ -116,6 +116,9 @@ def test_chains_alone(rules, n, longest, mean, lanes):
     # One step each.
     ([2048] * 4096, SHORT, SHORT), ([2048] * 4097, TILES, SHORT), ([1040] * 6144, TILES, SHORT),
     ([1024] * 60000, SHORT, SHORT),
+    # Units over 16 KiB have sixteen parts of 2 KiB, also where few.
+    ([32768], SHORT, SHORT), ([20000] * 8, SHORT, SHORT), ([32768] * 128, SHORT, SHORT),
+    ([32768] * 384, SHORT, SHORT), ([32769] * 8, TILES, TILES), ([32768] * 385, TILES, TILES),
     # More than two steps take a tile kernel's single wave too long.
     ([64] * 1500 + [8192], SHORT, SHORT), ([64] * 767 + [16384], SHORT, SHORT)])
 def test_short_launches_by_what_units_hold(rules, lengths, dec, ctr):
