@@ -1090,12 +1090,24 @@ int run_batch_noalloc(aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_s
 
 // ------------------------------------------------- single-op calls over tiles
 
-// Requests per chunk of a single-op call over tiles, and the smallest call
-// whose chunks are shared with the context's threads (below that, thread
-// hand-off costs more than it saves).
+// Requests per chunk of a single-op call over tiles, and how many threads a
+// context has for chunks at most.  (When they are used: launch_rules.h.)
 constexpr uint64_t PAR_CHUNK = 4096;
-constexpr uint64_t PAR_MIN_REQS = 4 * PAR_CHUNK;
 constexpr int PAR_MAX_THREADS = 8;
+
+// Whether the context's threads are there (made on first use).
+bool have_pool(aes_ctx *ctx) {
+    if (ctx->pool)
+        return true;
+    const unsigned hw = std::thread::hardware_concurrency();
+    const int t = (int)std::min<unsigned>(hw ? hw : 1, PAR_MAX_THREADS);
+    try {
+        ctx->pool.reset(new HostPool(t - 1));
+    } catch (...) {
+        return false;
+    }
+    return true;
+}
 
 struct ChunkScan {
     uint64_t err_at = UINT64_MAX;  // first request that breaks a rule
@@ -1133,21 +1145,11 @@ int single_tiles(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds, uint
     int st = check_buffers(d_in, d_out, buf_bytes, n, d_scheds);
     if (st)
         return st;
-    const bool threads = n >= PAR_MIN_REQS;
-    if (threads && !ctx->pool) {
-        const unsigned hw = std::thread::hardware_concurrency();
-        const int t = (int)std::min<unsigned>(hw ? hw : 1, PAR_MAX_THREADS);
-        try {
-            ctx->pool.reset(new HostPool(t - 1));
-        } catch (...) {
-            return 1;
-        }
-    }
     const uint32_t tile = ctx->tile_bytes;
     const bool dec = is_dec_tile_op(op);
     const uint64_t n_chunks = (n + PAR_CHUNK - 1) / PAR_CHUNK;
-    const auto run = [&](const auto &chunk) {
-        if (threads) {
+    const auto run = [&](bool threads, const auto &chunk) {
+        if (threads && have_pool(ctx)) {
             ctx->pool->run((int)n_chunks, chunk);
         } else {
             for (uint64_t c = 0; c < n_chunks; c++)
@@ -1163,7 +1165,7 @@ int single_tiles(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds, uint
         return AES_ERR_NOMEM;
     }
     // 1. Rules, order and unit counts per chunk.
-    run([&](int c) {
+    run(scan_in_threads(n), [&](int c) {
         ChunkScan k;
         const uint64_t lo = (uint64_t)c * PAR_CHUNK, hi = std::min(n, lo + PAR_CHUNK);
         for (uint64_t i = lo; i < hi; i++) {
@@ -1248,7 +1250,7 @@ int single_tiles(uint32_t op, aes_ctx *ctx, const aes_schedule_t *d_scheds, uint
             return st;
     }
     const auto put = [&](Unit *out) {
-        run([&](int c) {
+        run(write_in_threads(n, n_tiles), [&](int c) {
             const uint64_t lo = (uint64_t)c * PAR_CHUNK;
             write_single(op, offsets, lengths, key_idx, ivs, tile, lo, std::min(n, lo + PAR_CHUNK),
                          out + base[c]);

@@ -148,6 +148,18 @@ inline TileChoice choose_tiles(bool dec, uint32_t n_units, uint32_t max_bytes,
     return c;
 }
 
+// A single-op call over tiles shares its requests, 4,096 at a time, with a few
+// host threads: where there are many to check (8,192 requests of one tile 50 us
+// with the threads, 32 without, 16,384 equal), and where there are many units to
+// write (16,383 requests of 16 tiles, a call among others, 721 us with them, 772
+// without, while the kernels take about 700).
+constexpr uint64_t THREADS_MIN_REQS = 16384, THREADS_MIN_UNITS = 65536;
+inline bool scan_in_threads(uint64_t n_reqs) { return n_reqs >= THREADS_MIN_REQS; }
+inline bool write_in_threads(uint64_t n_reqs, uint64_t n_units) {
+    return n_reqs >= THREADS_MIN_REQS ||
+           (n_reqs >= THREADS_MIN_REQS / 2 && n_units >= THREADS_MIN_UNITS);
+}
+
 // Lanes per chain of a launch over n_chain chains (the longest of `longest`
 // bytes, `bytes` in all) that can put max_waves waves on the device for them: 1
 // unless `grouped`; 16 while every chain then runs at once, four chains to a

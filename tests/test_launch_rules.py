@@ -39,6 +39,9 @@ extern "C" int mixed_lanes(uint32_t n, uint32_t longest, int grouped, uint32_t n
                            uint64_t tile_bytes) {
     return mixed_chain_lanes(n, longest, (uint64_t)n * longest, grouped, n_wg, tile_bytes);
 }
+extern "C" int threads(uint64_t n, uint64_t units) {
+    return scan_in_threads(n) + 2 * write_in_threads(n, units);
+}
 extern "C" int lanes(uint32_t n, uint32_t longest, uint64_t bytes, int grouped, uint32_t waves) {
     return chain_lanes_for(n, longest, bytes, grouped, waves);
 }
@@ -191,3 +194,11 @@ def test_uneven_units_of_any_size(rules, per_cu, lo, hi):
         if parts >= per_cu * CUS:
             break
     assert choose(rules, units)[0] == UNEVEN
+
+
+@pytest.mark.parametrize("n,tiles,use", [
+    (1, 1, 0), (8191, 16, 0), (8192, 1, 0), (8192, 7, 0), (8192, 8, 2), (12000, 16, 2),
+    (16383, 1, 0), (16384, 1, 3), (65536, 1, 3), (1 << 20, 16, 3)])
+def test_host_threads(rules, n, tiles, use):
+    """Bit 0: the scan, bit 1: writing the unit records."""
+    assert rules.threads(ctypes.c_uint64(n), ctypes.c_uint64(n * tiles)) == use
