@@ -135,9 +135,13 @@ def _check(status: int, where: str):
 
 def _addr(a: np.ndarray) -> int:
     """The array's data address: a.ctypes.data, in a third to a half of its time
-    where the array's buffer can be taken as it is."""
-    if a.size and a.flags.c_contiguous and a.flags.writeable:
-        return ctypes.addressof(ctypes.c_char.from_buffer(a))
+    where the array's buffer can be taken as it is (not from a dtype that the
+    buffer protocol cannot describe, such as datetime64)."""
+    if a.nbytes and a.flags.c_contiguous and a.flags.writeable:
+        try:
+            return ctypes.addressof(ctypes.c_char.from_buffer(a))
+        except (ValueError, TypeError, BufferError):
+            pass
     return a.ctypes.data
 
 
