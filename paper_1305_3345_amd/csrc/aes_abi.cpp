@@ -898,11 +898,14 @@ int launch_table(aes_ctx *ctx, PlanView v, const Write &write, const aes_schedul
     v.enc_work.host_table = v.d_units == s->d_stage;
     v.d_preds = (Unit *)s->d_units + n;
     v.d_ctrs = s->d_ctrs;
-    if ((st = launch_planned(ctx, v, d_scheds, n_scheds, d_in, d_out, stream)))
-        return st;
-    HIP_TRY(hipEventRecord(s->ev, (hipStream_t)stream));
-    s->ev_pending = true;
-    return AES_OK;
+    st = launch_planned(ctx, v, d_scheds, n_scheds, d_in, d_out, stream);
+    // A launch that failed may have started kernels before: the slot is in use
+    // until the stream is past them all the same.
+    const hipError_t e = hipEventRecord(s->ev, (hipStream_t)stream);
+    s->ev_pending = e == hipSuccess;
+    if (e != hipSuccess)
+        (void)hipStreamSynchronize((hipStream_t)stream);
+    return st || e == hipSuccess ? st : hip_fail(e);
 }
 
 // A scanned batch as a PlanView without its memory.
