@@ -129,7 +129,8 @@ typedef struct aes_req {
 
 /* Batched service call (paper sections 2 and 3.3: many independent buffers
  * in one GPU launch).  d_scheds: device array of n_scheds schedules.
- * d_in, d_out: device buffers of buf_bytes bytes.  reqs: host array of
+ * d_in, d_out: device buffers of buf_bytes bytes, on any address (small
+ * launches are faster where both are 16-byte aligned).  reqs: host array of
  * n_reqs requests, validated, planned and copied before the call returns (to
  * kernel arguments, to the device, or to pinned staging that the kernels read).
  * Work is launched on stream; bytes of d_out outside every request are never
@@ -269,7 +270,10 @@ void aes_plan_destroy(aes_plan_t *plan);
  * CBC-decrypt tiles 2 blocks per lane x 1024 threads, chains several lanes
  * each (chain_quad = 1; chain_lanes = 64 when it is 0) x 256 threads, fused kernel
  * 1 block per lane, fuse = 1, grid = 0 (one workgroup per compute unit),
- * ctr_variant = AES_CTR_TABLE. */
+ * ctr_variant = AES_CTR_TABLE.  With the default shape of a tile kernel and grid
+ * 0, launches that other kernels run faster (short ones, uneven ones) go to
+ * those; any other shape or grid is kept for every launch of the context, small
+ * calls included. */
 typedef struct aes_launch_config {
     uint32_t tile_bytes;  /* bytes per CTR / CBC-decrypt unit: multiple of 1024 */
     uint32_t ctr_nb;      /* CTR tile kernel: 16-byte blocks per lane per step (1, 2, 4) */
@@ -322,7 +326,7 @@ int aes_ctx_set_config(aes_ctx_t *ctx, const aes_launch_config_t *cfg);
  * time and only over knobs the batch's launch uses: the tile size (batches
  * with tiles), the fusion switch (chains mixed with tiles), the tile-kernel
  * shapes (unfused launches of table tiles), the fused kernel's blocks per
- * lane (fused launches), chain lanes or four-lane chains (batches with
+ * lane (fused launches), chain lanes or several lanes per chain (batches with
  * CBC-encrypt chains) and the CTR variant (batches with CTR requests).  A
  * candidate replaces the best so far only when it is more than 2% faster,
  * so knobs that do not change the batch's time keep their starting values.  Leaves the chosen

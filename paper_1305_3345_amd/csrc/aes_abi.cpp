@@ -3,9 +3,10 @@
 // A call follows the service-request path of the paper (section 3.2): the
 // caller hands over input and output buffers and a request list; the library
 // checks every request on the host, cuts the requests into work units
-// (section 2: one launch carries one large task or many small tasks), copies
-// the unit table to the device through pinned staging and launches the round
-// kernels on the caller's stream.
+// (section 2: one launch carries one large task or many small tasks), hands the
+// unit table over (among the kernel arguments, in pinned staging that the
+// kernels read, or uploaded) and launches the round kernels on the caller's
+// stream.
 #include <hip/hip_runtime.h>
 #include <sched.h>
 #include <stdlib.h>
@@ -546,10 +547,9 @@ struct PlanView {
     bool zero_ctrs;  // the counters may not be zero: clear what a launch uses first
 };
 
-// units: the table to launch from, d_units: the device allocation (its
-// snapshots follow the place of the table in it).
-PlanView view_of(const Planned &p, const void *units, void *d_units, uint32_t *d_ctrs) {
-    return PlanView{units, (Unit *)d_units + (p.dec.size() + p.ctr.size() + p.chains.size()),
+// d_units: the table in device memory, with the snapshots behind it.
+PlanView view_of(const Planned &p, void *d_units, uint32_t *d_ctrs) {
+    return PlanView{d_units, (Unit *)d_units + (p.dec.size() + p.ctr.size() + p.chains.size()),
                     d_ctrs, p.dec.size(), p.ctr.size(), p.chains.size(), p.dec_has_pred_in,
                     p.dec_bytes, p.ctr_bytes, p.chain_bytes, p.chains.empty() ? 0u : p.chains[0].nbytes,
                     p.max_tile, p.dec_work, p.enc_work, p.n_ecb, false};
@@ -965,10 +965,9 @@ int run_batch(aes_ctx *ctx, const aes_schedule_t *d_scheds, uint32_t n_scheds,
         return st;
     if (ctx->device == AES_DEVICE_NONE)
         return AES_ERR_DEVICE;
-    if (n_units <= INLINE_UNITS) {
+    if (n_units <= INLINE_UNITS && !v.n_chain) {  // (launch_few takes no chains)
         Unit few[INLINE_UNITS];
-        ChainKey keys[2 * INLINE_UNITS];
-        write_units(reqs, n, tile, b, few, keys);
+        write_units(reqs, n, tile, b, few, nullptr);
         if (launch_few(ctx, few, v, d_scheds, n_scheds, d_in, d_out, stream, &st))
             return st;
     }
@@ -1543,7 +1542,7 @@ int aes_plan_launch(aes_plan_t *plan, const aes_schedule_t *d_scheds, const uint
     if (ctx->device == AES_DEVICE_NONE)
         return AES_ERR_DEVICE;
     HIP_TRY(hipSetDevice(ctx->device));
-    return launch_planned(ctx, view_of(plan->p, plan->d_units, plan->d_units, plan->d_ctrs),
+    return launch_planned(ctx, view_of(plan->p, plan->d_units, plan->d_ctrs),
                           d_scheds, plan->n_scheds, d_in, d_out, stream);
 }
 
@@ -1655,9 +1654,9 @@ int aes_ctx_set_config(aes_ctx_t *ctx, const aes_launch_config_t *cfg) {
 
 namespace {
 
-// Bytes per unit of a request's own launch.  In place, a multi-tile CBC
-// decryption stays in one wave, which carries each predecessor block in
-// registers before overwriting it.
+// Bytes per unit of a request's own launch, where the kernel for short ones does
+// not take it.  In place, a multi-tile CBC decryption then stays in one wave,
+// which carries each predecessor block in registers before overwriting it.
 uint32_t request_tile(const aes_ctx *ctx, const aes_req_t &r, bool in_place) {
     return r.op == AES_OP_CBC_DEC && in_place && r.length > ctx->tile_bytes ? (uint32_t)r.length
                                                                             : ctx->tile_bytes;
@@ -1747,7 +1746,7 @@ int aes_plan_graph(aes_plan_t *plan, const aes_schedule_t *d_scheds, const uint8
     if (!g)
         return AES_ERR_NOMEM;
     g->has_plan = plan->p.payload != 0;
-    g->view = view_of(plan->p, plan->d_units, plan->d_units, plan->d_ctrs);
+    g->view = view_of(plan->p, plan->d_units, plan->d_ctrs);
     *out = g;
     return AES_OK;
 }
@@ -1855,7 +1854,7 @@ int time_plan(aes_plan *plan, const aes_schedule_t *d_scheds, const uint8_t *d_i
         hipError_t e = hipEventRecord(a, ctx->capture);
         if (e == hipSuccess) {
             st = launch_planned(ctx,
-                                view_of(plan->p, plan->d_units, plan->d_units, plan->d_ctrs),
+                                view_of(plan->p, plan->d_units, plan->d_ctrs),
                                 d_scheds, plan->n_scheds, d_in, d_out, ctx->capture);
             if (!st)
                 e = hipEventRecord(b, ctx->capture);

@@ -111,7 +111,8 @@ int launch_cbcenc_chains(const Unit *d_units, uint32_t n_units, uint32_t longest
 // One launch over a mixed batch (nb = 1 or 2; 1024-thread workgroups).
 int launch_mixed(const MixedArgs &a, int nb, int grid, void *stream);
 // One request passed by value (the per-request launch form); tile = bytes per
-// unit (the whole request length keeps an in-place CBC decryption in one wave).
+// unit where the kernel for short launches does not take it (the whole request
+// length then keeps an in-place CBC decryption in one wave).
 int launch_request(const aes_req_t &r, uint32_t tile, const aes_schedule_t *d_sched,
                    uint32_t n_sched, const uint32_t *d_timg, const uint8_t *d_in,
                    uint8_t *d_out, int n_cu, void *stream);

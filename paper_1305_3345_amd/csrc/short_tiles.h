@@ -23,7 +23,8 @@
 namespace aesgpu {
 
 // 16 bytes at byte offset off of [base, base + nbytes), zeros for blocks not
-// inside (nbytes a multiple of 16): a buffer load, so there is no branch.
+// inside (nbytes a multiple of 16): a buffer load, so there is no branch.  base is
+// 16-byte aligned (aligned16 in launch_rules.h).
 __device__ __forceinline__ void buffer_block(const uint8_t *base, uint32_t nbytes, uint32_t off,
                                              uint32_t x[4]) {
     const __amdgpu_buffer_rsrc_t r =
